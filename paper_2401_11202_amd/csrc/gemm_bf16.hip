@@ -228,8 +228,13 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
       const uint32_t kvalid = (uint32_t)min(max(k_end - kb, 0), BK);
       char* base = smem + stage * STAGE + lds_w;
       __amdgpu_buffer_rsrc_t rma, rmb;
-      if (AMN) rma = make_rsrc(p.A + (int64_t)kb * p.lda + row0, kvalid * (uint32_t)p.lda * 2);
-      if (BMN) rmb = make_rsrc(Bg + (int64_t)kb * p.ldb + col0, kvalid * (uint32_t)p.ldb * 2);
+      // the last k row ends at the operand's last column (a ragged last tile
+      // would otherwise read past the end of the array)
+      auto bytes = [&](int64_t ld, int left) {
+        return kvalid ? (uint32_t)(((int64_t)(kvalid - 1) * ld + left) * 2) : 0u;
+      };
+      if (AMN) rma = make_rsrc(p.A + (int64_t)kb * p.lda + row0, bytes(p.lda, p.M - row0));
+      if (BMN) rmb = make_rsrc(Bg + (int64_t)kb * p.ldb + col0, bytes(p.ldb, p.N - col0));
       const uint32_t kmask = (kb + lchunk * 8 < k_end) ? 0u : OOB;
       const uint32_t so = (uint32_t)kb * 2;
 #pragma unroll
