@@ -369,7 +369,7 @@ def _cpu_sample(w, x, target_s, cores):
 # summary stays valid while these files are unchanged.
 _COMMON = ("kernels.h", "partir_api.cpp")
 _ROLE_SOURCES = {
-    "gemm": ("gemm_bf16.hip", "device_math.h", "lds_dma.h") + _COMMON,
+    "gemm": ("gemm_bf16.hip", "gemm_bf16_tile.hip", "device_math.h", "lds_dma.h") + _COMMON,
     "attn.core": ("attention.hip", "lds_dma.h") + _COMMON,
     "attn.combine": ("attention.hip", "lds_dma.h") + _COMMON,
     "attn.bwd": ("attention_bwd.hip", "lds_dma.h") + _COMMON,

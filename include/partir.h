@@ -93,7 +93,7 @@ typedef enum partir_b_layout {
 
 /* Realisation of a #sum loop on the device. */
 typedef enum partir_sum_impl {
-  PARTIR_SUM_AUTO = 0,   /* chosen by the planner from the output tile count              */
+  PARTIR_SUM_AUTO = 0,   /* chosen by the planner from the output's size and K            */
   PARTIR_SUM_FUSED = 1,  /* shard K-ranges accumulate, r ascending, in one MFMA accumulator */
   PARTIR_SUM_SPLITK = 2  /* each shard writes an fp32 partial; an ordered reduce sums them  */
 } partir_sum_impl;

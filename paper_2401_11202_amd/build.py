@@ -29,7 +29,10 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # accumulator sets live at once; left to its heuristics the compiler parks
 # values in accumulation registers and copies them around every MFMA, so its
 # MFMAs are asked to use ordinary vector registers.
-EXTRA = {"attention_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]}
+# (the same for the small GEMM tiles, one workgroup per CU of which may use
+# the whole register file)
+EXTRA = {"attention_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=true"],
+         "gemm_bf16_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]}
 
 
 def hipcc() -> str:

@@ -1,7 +1,7 @@
 // bf16 MFMA GEMM for gfx950: C = A . B^T, A K-contiguous or stored [K, M],
 // B K-contiguous or stored [K, N].
 //
-// One workgroup computes a 256x256 output tile of one virtual shard with eight
+// One workgroup computes a 256x256 output tile with eight
 // waves (2 x 4, two per SIMD), each owning a 128x64 sub-tile as 8 x 4
 // accumulators of v_mfma_f32_16x16x32_bf16.  K advances in 64-wide tiles
 // through LDS buffers filled by buffer loads that write LDS directly (no
@@ -15,8 +15,9 @@
 // keeps L2 -> LDS traffic per FLOP minimal.
 //
 // Loop semantics realised here (PartIR:Core, Sec. 5 / App. C):
-//  * #tile over M or N: the grid enumerates every shard's tiles; a tile never
-//    straddles a shard and stores into the shard's slice of C.
+//  * #tile over M or N: the shards are adjacent slices, so the grid's tiles
+//    cover the whole output; a tile may span shards and stores into each one's
+//    slice of C.
 //  * #sum over K, fused: the shards' K-ranges are consecutive, so one tile's
 //    K loop walks shard 0, 1, ..., R-1 in order into one accumulator.
 //  * #sum over K, split: the grid also enumerates the K shards and each writes
@@ -103,7 +104,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS bases and M0 in SGPRs
   const int wm = wave >> 2, wn = wave & 3;
 
-  // ---- which tile of which virtual shard ----------------------------------
+  // ---- which tile ----------------------------------------------------------
   const int ntiles = p.tiles_m * p.tiles_n;
   int bid = blockIdx.x;
   const int nwg = gridDim.x;
@@ -139,16 +140,13 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   const int tm = first_m + rr % gm;
   const int tn = rr / gm;
 
-  const int sm = tm / p.tpm, tmi = tm - sm * p.tpm;
-  const int row0 = sm * p.ms + tmi * BM;
-  const int rows = min(BM, p.ms - tmi * BM);
-  const int per_gn = p.rn * p.tpn;
-  const int grp = tn / per_gn, rem = tn - grp * per_gn;
-  const int sn = rem / p.tpn, tni = rem - sn * p.tpn;
-  const int col0 = sn * p.ns + tni * BN;
-  const int cols = min(BN, p.ns - tni * BN);
+  const int row0 = tm * BM;
+  const int rows = min(BM, p.M - row0);
+  const int grp = tn / p.tpn;
+  const int col0 = (tn - grp * p.tpn) * BN;
+  const int cols = min(BN, p.N - col0);
   int k_begin = (p.nsplit > 1) ? split * p.ks : 0;
-  int k_end = (p.nsplit > 1) ? k_begin + p.ks : p.K;
+  int k_end = (p.nsplit > 1) ? min(p.K, k_begin + p.ks) : p.K;
   if (tail_unit >= 0) {
     k_begin = tail_part * p.tail_kt * BK;
     k_end = min(p.K, k_begin + p.tail_kt * BK);

@@ -19,9 +19,10 @@ enum GemmEpi : int {
 //   A : [M, K] bf16 row-major, leading dim lda.
 //   B : per group g, B_g^T stored [N, K] bf16 row-major (leading dim ldb).
 //   C : per group g, [M, N] row-major (leading dim ldc).
-// Shards: rm #tile shards along M (extent ms each), rn along N (extent ns),
-// rk #sum shards along K (extent ks).  Output tiles never straddle a shard:
-// tpm / tpn tiles per shard (the last one may be partial).
+// The #tile shards along M and N are adjacent slices of A, B and C, so the
+// output tiles run over the whole [M, N] (per group) and may span shards.
+// A #sum along K is one accumulator (nsplit = 1) or nsplit fp32 partials over
+// consecutive K ranges of ks.
 struct GemmParams {
   const uint16_t* A;
   const uint16_t* B[3];
@@ -32,11 +33,10 @@ struct GemmParams {
   void* aux;       // EPI_BF16_SAVE: pre-activation output (group 0, leading dim ldc)
   int64_t lda, ldb, ldc, ldr, part_ld, part_stride;
   int M, N, K, ngroups;
-  int rm, ms, tpm;
-  int rn, ns, tpn;
-  int rk, ks;
-  int tiles_m, tiles_n;
-  int nsplit;      // 1: the rk shards accumulate in order in one accumulator
+  int tile;        // output tile edge: 256 (gemm_bf16.hip), 128 or 64 (gemm_bf16_tile.hip)
+  int tpn;         // tile columns per group
+  int tiles_m, tiles_n;   // tiles_n = ngroups * tpn
+  int nsplit, ks;
   int group_m;     // tile-order grouping for L2 reuse
   int act;         // 0 none, 1 gelu-erf
   int epi;         // GemmEpi
@@ -81,6 +81,9 @@ struct GemmParts {
   int b_nrows, b_kcols, b_nk, b_gstride;
   int c_rows;
 };
+// The same product in 128x128 or 64x64 tiles (p.tile); t: device-local
+// arrays or NULL.
+hipError_t launch_gemm_bf16_tile(const GemmParams& p, const GemmParts* t, hipStream_t s);
 hipError_t launch_gemm_bf16_parts(const GemmParams& p, const GemmParts& t, hipStream_t s);
 hipError_t launch_gemm_bf16_parts_fixup(const GemmParams& p, const GemmParts& t, hipStream_t s);
 int gemm_bf16_tile_m();

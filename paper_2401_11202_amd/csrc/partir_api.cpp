@@ -41,6 +41,9 @@ constexpr int kNumCU = 256;           // MI355X compute units: a grid below this
 // (a 2 x 16 block needs 18): the least L2 -> fabric traffic per k step.
 int group_m_for(int /*tiles_n*/) { return 4; }
 constexpr size_t kWsAlign = 256;
+// Partials the planner may ask for on its own: what the array of
+// partir_loop_matmul_noalloc holds.
+constexpr size_t kMaxPartialBytes = (size_t)64 << 20;
 
 thread_local std::string g_error;
 thread_local std::string g_plan_text;
@@ -126,24 +129,30 @@ struct GemmSpec {
   int sum_impl = PARTIR_SUM_AUTO;
   void* aux = nullptr;          // bf16 pre-activation output (kept for a backward pass)
   bool tail_ok = false;         // the caller's workspace region holds gemm_ws_bytes (tail split allowed)
+  bool split_ok = false;        // ... and one plain C (and residual) takes the ordered reduction of K parts
   bool a_mn = false;            // bf16 A stored [K, M] (leading dim lda) instead of [M, K]
   const char* name = "gemm";    // role, used as the trace name
   const char* label = "gemm";   // loop nest, for the plan text
 };
 
-int64_t gemm_tiles(const GemmSpec& g) {
-  const int64_t tile = g.ab_dtype == PARTIR_BF16 ? gemm_bf16_tile_m() : gemm_f32_tile();
-  return g.rm * cdiv(g.M / g.rm, tile) * g.ngroups * g.rn * cdiv(g.N / g.rn, tile);
+// Output tiles of edge `tile`.  The #tile shards are adjacent slices, so the
+// tiles run over the whole output (per group) and only its far edges are
+// ragged, not every shard's.
+int64_t gemm_tiles(const GemmSpec& g, int64_t tile) {
+  return cdiv(g.M, tile) * g.ngroups * cdiv(g.N, tile);
 }
 
+// PARTIR_SUM_AUTO: a #sum is split when the output has too few tiles (counted
+// per #tile shard, in 256-wide bf16 or 64-wide fp32 tiles) to fill the chip.
 bool gemm_uses_splitk(const GemmSpec& g) {
   if (g.rk <= 1) return false;
   if (g.sum_impl == PARTIR_SUM_SPLITK) return true;
   if (g.sum_impl == PARTIR_SUM_FUSED) return false;
-  return gemm_tiles(g) < kNumCU;   // too few output tiles: spread the K shards too
+  const int64_t tile = g.ab_dtype == PARTIR_BF16 ? gemm_bf16_tile_m() : gemm_f32_tile();
+  return g.rm * cdiv(g.M / g.rm, tile) * g.ngroups * g.rn * cdiv(g.N / g.rn, tile) < kNumCU;
 }
 
-// Load balance of the last wave: with ntiles = q * kNumCU + r output tiles
+// Load balance of the last wave of 256-wide tiles: with ntiles = q * kNumCU + r output tiles
 // (0 < r <= kNumCU / 2), the r tiles of the partial last wave run as `parts`
 // workgroups each over consecutive K ranges, so the last wave holds
 // r * parts <= kNumCU shorter workgroups instead of r whole ones; a fixup
@@ -151,8 +160,9 @@ bool gemm_uses_splitk(const GemmSpec& g) {
 // epilogue.  Returns parts (1: no split) and the first split tile.
 int gemm_tail_parts(const GemmSpec& g, int64_t* tail_base) {
   *tail_base = 0;
-  if (!g.tail_ok || g.ab_dtype != PARTIR_BF16 || gemm_uses_splitk(g)) return 1;
-  const int64_t ntiles = gemm_tiles(g), r = ntiles % kNumCU, nk = cdiv(g.K, 64);
+  if (!g.tail_ok || g.ab_dtype != PARTIR_BF16) return 1;
+  const int64_t ntiles = gemm_tiles(g, gemm_bf16_tile_m()), r = ntiles % kNumCU, nk = cdiv(g.K, 64);
+  if (g.split_ok && ntiles < kNumCU) return 1;   // less than one wave: gemm_tiling splits every tile instead
   int parts = 1;
   while (parts < 4 && 2 * parts * r <= kNumCU && nk >= 2 * parts * 8) parts *= 2;   // >= 8 K tiles a part
   if (r == 0 || parts == 1 || (r * parts) % 8) return 1;   // the XCD schedule wants multiples of 8
@@ -160,11 +170,74 @@ int gemm_tail_parts(const GemmSpec& g, int64_t* tail_base) {
   return parts;
 }
 
-size_t gemm_ws_bytes(const GemmSpec& g) {
-  if (gemm_uses_splitk(g)) return align_up((size_t)g.rk * g.M * g.N * sizeof(float));
+// How a bf16 product runs: the output tile, and the K ranges (1: one
+// accumulator per output) whose fp32 partials an ordered reduction adds.
+struct GemmTiling {
+  int tile = 256;
+  int parts = 1;
+  int64_t ks = 0;    // K extent of a part
+};
+
+// Time of a bf16 product in microseconds, from the tiles a CU runs one after
+// the other (n) and the 64-wide K tiles of each (nk).  The constants are
+// fitted to measurements (MI355X, B as [N, K] and [K, N], time of the launch):
+//   tile 256  1 x 64: 95, 1 x 40: 62, 2 x 24: 89     one workgroup per CU
+//   tile 128  1 x 32: 24, 1 x 64: 43, 1 x 128: 78, 3 x 32: 50, 4 x 64: 120
+//   tile 64   1 x 16: 10, 1 x 256: 73, 4 x 32: 33    n > 1: up to two at a time
+// A 256 tile does the most work per byte moved through LDS (1450 TFLOP/s on
+// full waves against 1200 and 700), so the small tiles pay where its grid
+// leaves CUs idle.  A K split adds the partials' traffic and a launch.
+double gemm_us(const GemmSpec& g, int tile, int parts) {
+  const int64_t nk = cdiv(cdiv(g.K, 64), parts);
+  const int64_t units = gemm_tiles(g, tile) * parts;
+  const double n = (double)cdiv(units, kNumCU);
+  double t;
   int64_t base;
-  const int parts = gemm_tail_parts(g, &base);
-  return parts > 1 ? align_up((size_t)(gemm_tiles(g) - base) * parts * kGemmTailPartBytes) : 0;
+  const int tail = tile == 256 && parts == 1 ? gemm_tail_parts(g, &base) : 1;
+  if (tile == 256) t = 3 + (tail > 1 ? n - 1 + 1.0 / tail : n) * (6 + 1.38 * nk) + (tail > 1 ? 5 + 10 * tail : 0);
+  else if (tile == 128) t = 5 + (n == 1 ? 0.55 * nk : n * (1 + 0.42 * nk));
+  else t = 5 + std::max(0.27 * nk, n * (0.5 + 0.2 * nk));
+  if (parts > 1) t += 5 + 8.0 * parts * g.M * g.N / 5.5e6;   // 5.5 MB/us, written and read
+  return t;
+}
+
+GemmTiling gemm_tiling(const GemmSpec& g) {
+  GemmTiling best;
+  best.ks = g.K;
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return best;   // nothing to launch
+  const int64_t nk = cdiv(g.K, 64);
+  const bool shard_parts = g.rk > 1 && g.sum_impl == PARTIR_SUM_SPLITK;   // one partial per #sum shard
+  // a product without a #sum whose output is one 256-wide tile needs no workspace
+  const bool may_split = g.split_ok && (g.rk > 1 || gemm_tiles(g, 256) > 1);
+  double best_us = 0;
+  for (int tile = 256; tile >= 64; tile /= 2) {
+    for (int want = 1; want <= 4; want *= 2) {
+      const int64_t kt = cdiv(nk, want);
+      const int parts = shard_parts ? g.rk : (int)cdiv(nk, kt);
+      if (!shard_parts && want > 1 && (!may_split || parts != want || kt < 4 ||
+                                       (size_t)parts * g.M * g.N * sizeof(float) > kMaxPartialBytes)) continue;
+      const double us = gemm_us(g, tile, parts);
+      if (best_us == 0 || us < (tile == best.tile ? 1.0 : 0.95) * best_us) {   // the larger tile near a tie
+        best_us = us;
+        best.tile = tile;
+        best.parts = parts;
+        best.ks = shard_parts ? g.K / g.rk : (parts > 1 ? kt * 64 : g.K);
+      }
+      if (shard_parts) break;
+    }
+  }
+  return best;
+}
+
+// Workspace of one GEMM: split-K partials, or the tail parts of 256-wide tiles.
+size_t gemm_ws_bytes(const GemmSpec& g) {
+  if (g.ab_dtype != PARTIR_BF16)
+    return gemm_uses_splitk(g) ? align_up((size_t)g.rk * g.M * g.N * sizeof(float)) : 0;
+  const GemmTiling c = gemm_tiling(g);
+  if (c.parts > 1) return align_up((size_t)c.parts * g.M * g.N * sizeof(float));
+  int64_t base;
+  const int tail = c.tile == 256 ? gemm_tail_parts(g, &base) : 1;
+  return tail > 1 ? align_up((size_t)(gemm_tiles(g, 256) - base) * tail * kGemmTailPartBytes) : 0;
 }
 
 std::string describe_gemm(const GemmSpec& g, int64_t grid, bool split) {
@@ -191,15 +264,17 @@ std::string describe_gemm(const GemmSpec& g, int64_t grid, bool split) {
 // points at this GEMM's region of gemm_ws_bytes(g) bytes (split-K partials or
 // the tail parts).
 int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
-  const bool split = gemm_uses_splitk(g);
+  const bool bf16 = g.ab_dtype == PARTIR_BF16;
+  const GemmTiling c = bf16 ? gemm_tiling(g) : GemmTiling{};
+  const bool split = bf16 ? c.parts > 1 : gemm_uses_splitk(g);
+  const int nparts = bf16 ? c.parts : (split ? g.rk : 1);
   if (g.rk > 1) {
     plan.n_sum_loops += 1;
     if (split) plan.n_sum_splitk += 1;
   }
   const int epi_store = g.resid_add ? EPI_RESID_F32 : (g.c_dtype == PARTIR_BF16 ? EPI_BF16 : EPI_F32);
   Launch L;
-  if (g.ab_dtype == PARTIR_BF16) {
-    const int tile = gemm_bf16_tile_m();
+  if (bf16) {
     GemmParams& p = L.gemm;
     p.A = (const uint16_t*)g.A;
     for (int i = 0; i < 3; ++i) {
@@ -213,21 +288,19 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.ldr = g.ldr;
     p.part_ld = g.N; p.part_stride = g.M * g.N;
     p.M = (int)g.M; p.N = (int)g.N; p.K = (int)g.K; p.ngroups = g.ngroups;
-    p.rm = g.rm; p.ms = (int)(g.M / g.rm); p.tpm = (int)cdiv(p.ms, tile);
-    p.rn = g.rn; p.ns = (int)(g.N / g.rn); p.tpn = (int)cdiv(p.ns, tile);
-    p.rk = g.rk; p.ks = (int)(g.K / g.rk);
-    p.tiles_m = p.rm * p.tpm;
-    p.tiles_n = g.ngroups * p.rn * p.tpn;
-    p.nsplit = split ? g.rk : 1;
+    p.tile = c.tile;
+    p.tpn = (int)cdiv(g.N, c.tile);
+    p.tiles_m = (int)cdiv(g.M, c.tile);
+    p.tiles_n = g.ngroups * p.tpn;
+    p.nsplit = c.parts; p.ks = (int)c.ks;
     p.group_m = group_m_for(p.tiles_n);
     p.act = split ? 0 : g.act;
-    // a kept pre-activation needs the whole K sum in the tile (never split:
-    // only the up-projection, which has no #sum, asks for it)
+    // a kept pre-activation needs the whole K sum in the tile (never split)
     p.epi = split ? EPI_PARTIAL : (g.aux ? EPI_BF16_SAVE : epi_store);
     p.a_mn = g.a_mn;
     p.b_mn = !g.b_nk;   // B stored [K, N]
-    int64_t tail_base;
-    p.tail_parts = gemm_tail_parts(g, &tail_base);
+    int64_t tail_base = 0;
+    p.tail_parts = c.tile == 256 && !split ? gemm_tail_parts(g, &tail_base) : 1;
     p.tail_base = (int)tail_base;
     p.tail_kt = (int)cdiv(cdiv(g.K, 64), p.tail_parts);
     p.tail_ws = p.tail_parts > 1 ? (float*)ws : nullptr;
@@ -236,8 +309,17 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     const int64_t ntiles = (int64_t)p.tiles_m * p.tiles_n;
     L.text = describe_gemm(g, p.tail_parts > 1 ? tail_base + (ntiles - tail_base) * p.tail_parts : ntiles * p.nsplit,
                            split);
+    char buf[200];
+    if (split && g.sum_impl != PARTIR_SUM_SPLITK) {   // counted in 256 x 256 output tiles, like the tail split
+      snprintf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %lld K tiles each",
+               (long long)gemm_tiles(g, 256), c.parts, (long long)(c.ks / 64));
+      L.text += buf;
+    }
+    if (c.tile != 256) {
+      snprintf(buf, sizeof buf, "; workgroup tiles of %d x %d", c.tile, c.tile);
+      L.text += buf;
+    }
     if (p.tail_parts > 1) {
-      char buf[200];
       snprintf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %d K tiles each",
                (long long)(ntiles - tail_base), p.tail_parts, p.tail_kt);
       L.text += buf;
@@ -275,11 +357,11 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
   if (split) {
     Launch R;
     R.kind = L_REDUCE;
-    R.name = std::string(g.name) + ".reduce";
+    R.name = std::string(g.name) + (g.rk > 1 ? ".reduce" : ".fixup");
     ReduceParams& r = R.reduce;
     r.partial = (const float*)ws;
     r.part_ld = g.N; r.part_stride = g.M * g.N;
-    r.R = g.rk; r.M = (int)g.M; r.N = (int)g.N;
+    r.R = nparts; r.M = (int)g.M; r.N = (int)g.N;
     r.C = g.C[0]; r.ldc = g.ldc;
     r.bias = g.bias[0];
     r.resid = g.resid; r.ldr = g.ldr;
@@ -287,9 +369,13 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     r.out_bf16 = (!g.resid_add && g.c_dtype == PARTIR_BF16);
     r.resid_add = g.resid_add;
     char buf[256];
-    snprintf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum_{r=0..%d} partial[r] (in-device all_reduce)%s%s",
-             (long long)g.M, (long long)g.N, g.rk - 1, g.bias[0] ? " + bias" : "",
-             g.resid_add ? " + residual" : "");
+    if (g.rk > 1)
+      snprintf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum_{r=0..%d} partial[r] (in-device all_reduce)%s%s",
+               (long long)g.M, (long long)g.N, nparts - 1, g.bias[0] ? " + bias" : "",
+               g.resid_add ? " + residual" : "");
+    else
+      snprintf(buf, sizeof buf, "%s: C[%lld,%lld] = sum of the %d K parts in ascending order, then the epilogue",
+               R.name.c_str(), (long long)g.M, (long long)g.N, nparts);
     R.text = buf;
     plan.launches.push_back(R);
     return 2;
@@ -302,7 +388,7 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
 // ---------------------------------------------------------------------------
 hipError_t run_one(const Launch& L, hipStream_t s) {
   switch (L.kind) {
-    case L_GEMM_BF16: return launch_gemm_bf16(L.gemm, s);
+    case L_GEMM_BF16: return L.gemm.tile == 256 ? launch_gemm_bf16(L.gemm, s) : launch_gemm_bf16_tile(L.gemm, nullptr, s);
     case L_GEMM_F32: return launch_gemm_f32(L.gemm32, s);
     case L_REDUCE: return launch_splitk_reduce(L.reduce, s);
     case L_ATTN: return launch_attention(L.attn, s);
@@ -310,7 +396,9 @@ hipError_t run_one(const Launch& L, hipStream_t s) {
     case L_RMS: return launch_rmsnorm(L.rms, s);
     case L_ACT_BWD: return launch_act_backward(L.act, s);
     case L_COLSUM: return launch_colsum(L.cs, s);
-    case L_GEMM_BF16_PARTS: return launch_gemm_bf16_parts(L.gemm, *L.parts, s);
+    case L_GEMM_BF16_PARTS:
+      return L.gemm.tile == 256 ? launch_gemm_bf16_parts(L.gemm, *L.parts, s)
+                                : launch_gemm_bf16_tile(L.gemm, L.parts.get(), s);
     case L_GEMM_BF16_FIXUP: return launch_gemm_bf16_fixup(L.gemm, s);
     case L_GEMM_BF16_PARTS_FIXUP: return launch_gemm_bf16_parts_fixup(L.gemm, *L.parts, s);
     case L_ATTN_BWD: return launch_attention_backward(L.attn_bwd, s);
@@ -468,15 +556,22 @@ GemmSpec matmul_spec(const MatmulArgs& a) {
   g.rn = a.tile_axis == PARTIR_AXIS_N ? a.R : 1;
   g.rk = a.sum_axis == PARTIR_AXIS_K ? a.R : 1;
   g.sum_impl = a.sum_impl;
-  g.tail_ok = true;
+  g.tail_ok = g.split_ok = true;
   g.name = a.ab == PARTIR_BF16 ? "loop_matmul.bf16" : "loop_matmul.f32";
   g.label = "loop_matmul";
   return g;
 }
 
+// A split #sum asks for the partials of every shard, also where the planner
+// then needs fewer.
+size_t matmul_ws_bytes(const GemmSpec& g) {
+  const size_t need = gemm_ws_bytes(g);
+  return gemm_uses_splitk(g) ? std::max(need, align_up((size_t)g.rk * g.M * g.N * sizeof(float))) : need;
+}
+
 void plan_matmul(const MatmulArgs& a, void* ws, Plan& plan) {
   GemmSpec g = matmul_spec(a);
-  plan.ws_bytes = gemm_ws_bytes(g);
+  plan.ws_bytes = matmul_ws_bytes(g);
   plan.n_shards = g.rm * g.rn * g.rk;
   plan.n_tile_loops = a.tile_axis != PARTIR_AXIS_NONE;
   plan.flops = 2.0 * a.M * a.N * a.K;
@@ -532,16 +627,18 @@ void plan_mlp(const MlpArgs& a, void* ws, Plan& plan) {
   g1.lda = a.D; g1.ldb = a.F; g1.ldc = a.F;
   g1.M = a.T; g1.N = a.F; g1.K = a.D;
   g1.c_dtype = PARTIR_BF16; g1.rm = a.Rb; g1.rn = a.Rm; g1.act = a.act; g1.aux = a.Z;
+  g1.tail_ok = true; g1.split_ok = !a.Z;
   g1.name = "mlp.up";
   g1.label = "mlp.up   H = act(slice 0 X[b] . slice 1 W1[m])";
   GemmSpec g2;
   g2.A = H; g2.B[0] = a.W2; g2.b_nk = 0; g2.C[0] = a.Y; g2.bias[0] = (const float*)a.b2;
   g2.lda = a.F; g2.ldb = a.D; g2.ldc = a.D;
   g2.M = a.T; g2.N = a.D; g2.K = a.F;
-  g2.c_dtype = a.out; g2.rm = a.Rb; g2.rk = a.Rm;
+  g2.c_dtype = a.out; g2.rm = a.Rb; g2.rk = a.Rm; g2.tail_ok = g2.split_ok = true;
   g2.name = "mlp.down";
   g2.label = "mlp.down Y = sum_m H[:, m] . slice 0 W2[m]";
-  plan.ws_bytes = h_bytes + gemm_ws_bytes(g2);
+  void* part = ws ? base + h_bytes : nullptr;   // split-K / tail parts, one GEMM at a time
+  plan.ws_bytes = h_bytes + std::max(gemm_ws_bytes(g1), gemm_ws_bytes(g2));
   plan.n_shards = a.Rb * a.Rm;
   plan.n_tile_loops = (a.Rb > 1) + 1;
   plan.flops = 4.0 * a.T * a.D * a.F;
@@ -552,8 +649,8 @@ void plan_mlp(const MlpArgs& a, void* ws, Plan& plan) {
     plan_empty_sum(a.Y, a.T, a.D, a.D, a.out == PARTIR_BF16, (const float*)a.b2, nullptr, 0, false, "mlp.down", plan);
     return;
   }
-  plan_gemm(g1, nullptr, plan);
-  plan_gemm(g2, ws ? base + h_bytes : nullptr, plan);
+  plan_gemm(g1, part, plan);
+  plan_gemm(g2, part, plan);
 }
 
 // ---------------------------------------------------------------------------
@@ -612,22 +709,18 @@ GemmSpec qkv_spec(const void* Xn, const void* Wq, const void* Wk, const void* Wv
   g.ngroups = 3;
   g.lda = D; g.ldb = D; g.ldc = D;
   g.M = T; g.N = D; g.K = D;
-  g.c_dtype = PARTIR_BF16; g.rm = Rb; g.rn = Rm;
+  g.c_dtype = PARTIR_BF16; g.rm = Rb; g.rn = Rm; g.tail_ok = true;
   g.name = "attn.qkv";
   g.label = "attn.qkv Q|K|V = slice 0 X[b] . slice 1 W{q,k,v}[m]";
   return g;
 }
 
-// QKV projection + attention core into (Q, K, V, O) inside the workspace.
-// With `gemm_ws` (gemm_ws_bytes of the tail-split qkv_spec) the projection
-// may split its last wave.
+// QKV projection + attention core into (Q, K, V, O) inside the workspace;
+// `gemm_ws`: gemm_ws_bytes of the projection.
 void plan_attention_core(const void* Xn, const void* Wq, const void* Wk, const void* Wv, char* qkvo,
                          int64_t B, int64_t S, int64_t D, int64_t H, int64_t dh, int causal, float scale,
-                         int Rb, int Rm, Plan& plan, float* lse = nullptr, bool tail = false,
-                         char* gemm_ws = nullptr) {
-  GemmSpec g = qkv_spec(Xn, Wq, Wk, Wv, qkvo, B * S, D, Rb, Rm);
-  g.tail_ok = tail;
-  plan_gemm(g, gemm_ws, plan);
+                         int Rb, int Rm, Plan& plan, float* lse, char* gemm_ws) {
+  plan_gemm(qkv_spec(Xn, Wq, Wk, Wv, qkvo, B * S, D, Rb, Rm), gemm_ws, plan);
   plan_attention_launch(qkvo, B, S, D, H, dh, causal, scale, Rm, plan, lse);
 }
 
@@ -672,22 +765,24 @@ void plan_attn(const AttnArgs& a, void* ws, Plan& plan) {
   const size_t core = a.saved ? 0 : attn_core_bytes(T, a.D);
   char* qkvo = a.saved ? (char*)a.saved : base;
   float* lse = a.saved ? (float*)((char*)a.saved + attn_core_bytes(T, a.D)) : nullptr;
+  char* part = base ? base + core : nullptr;   // split-K / tail parts, one GEMM at a time
   plan_attention_core(a.X, a.Wq, a.Wk, a.Wv, qkvo, a.B, a.S, a.D, a.H, a.dh, a.causal, a.scale, a.Rb, a.Rm, plan,
-                      lse);
+                      lse, part);
   GemmSpec g;
   g.A = qkvo ? qkvo + 3 * align_up((size_t)T * a.D * 2) : nullptr;
   g.B[0] = a.Wo; g.b_nk = 0; g.C[0] = a.Y;
   g.lda = a.D; g.ldb = a.D; g.ldc = a.D;
   g.M = T; g.N = a.D; g.K = a.D;
-  g.c_dtype = a.out; g.rm = a.Rb; g.rk = a.Rm;
+  g.c_dtype = a.out; g.rm = a.Rb; g.rk = a.Rm; g.tail_ok = g.split_ok = true;
   g.name = "attn.out";
   g.label = "attn.out Y = sum_m O[:, m heads] . slice 0 Wo[m]";
-  plan.ws_bytes = core + gemm_ws_bytes(g);
+  plan.ws_bytes = core + std::max(gemm_ws_bytes(qkv_spec(a.X, a.Wq, a.Wk, a.Wv, qkvo, T, a.D, a.Rb, a.Rm)),
+                                  gemm_ws_bytes(g));
   plan.n_shards = a.Rb * a.Rm;
   plan.n_tile_loops = (a.Rb > 1) + 1;
   const double pairs = a.causal ? (double)a.S * (a.S + 1) / 2 : (double)a.S * a.S;
   plan.flops = 8.0 * T * a.D * a.D + 4.0 * a.B * a.H * pairs * a.dh;
-  plan_gemm(g, base ? base + core : nullptr, plan);
+  plan_gemm(g, part, plan);
 }
 
 struct DecArgs {
@@ -744,18 +839,16 @@ void plan_dec(const DecArgs& a, void* ws, Plan& plan) {
   char* qkvo = base ? base + xn_bytes : nullptr;
   char* Hf = base ? base + xn_bytes + core : nullptr;
   char* part = base ? base + xn_bytes + core + h_bytes : nullptr;   // split-K / tail parts, one GEMM at a time
-  GemmSpec gq = qkv_spec(xn, a.Wq, a.Wk, a.Wv, qkvo, T, a.D, a.Rb, a.Rm);
-  gq.tail_ok = true;
-
+  const GemmSpec gq = qkv_spec(xn, a.Wq, a.Wk, a.Wv, qkvo, T, a.D, a.Rb, a.Rm);
   plan_rmsnorm((const float*)a.x, (const float*)a.g1, xn, T, a.D, a.eps, a.Rb, plan);
   plan_attention_core(xn, a.Wq, a.Wk, a.Wv, qkvo, a.B, a.S, a.D, a.H, a.dh, 1, 0.0f, a.Rb, a.Rm, plan, nullptr,
-                      true, part);
+                      part);
   GemmSpec go;
   go.A = qkvo ? qkvo + 3 * align_up((size_t)T * a.D * 2) : nullptr;
   go.B[0] = a.Wo; go.b_nk = 0; go.C[0] = a.x; go.resid = (const float*)a.x; go.resid_add = true;
   go.lda = a.D; go.ldb = a.D; go.ldc = a.D; go.ldr = a.D;
   go.M = T; go.N = a.D; go.K = a.D;
-  go.c_dtype = PARTIR_F32; go.rm = a.Rb; go.rk = a.Rm; go.tail_ok = true;
+  go.c_dtype = PARTIR_F32; go.rm = a.Rb; go.rk = a.Rm; go.tail_ok = go.split_ok = true;
   go.name = "attn.out";
   go.label = "dec.attn_out x += sum_m O[:, m heads] . slice 0 Wo[m]";
   plan_gemm(go, part, plan);
@@ -769,15 +862,15 @@ void plan_dec(const DecArgs& a, void* ws, Plan& plan) {
   g1.A = xn; g1.B[0] = a.W1; g1.b_nk = 0; g1.C[0] = Hf;
   g1.lda = a.D; g1.ldb = a.F; g1.ldc = a.F;
   g1.M = T; g1.N = a.F; g1.K = a.D;
-  g1.c_dtype = PARTIR_BF16; g1.rm = a.Rb; g1.rn = a.Rm; g1.act = 1;
+  g1.c_dtype = PARTIR_BF16; g1.rm = a.Rb; g1.rn = a.Rm; g1.act = 1; g1.tail_ok = g1.split_ok = true;
   g1.name = "mlp.up";
   g1.label = "dec.ffn_up H = gelu(slice 0 xn[b] . slice 1 W1[m])";
-  plan_gemm(g1, nullptr, plan);
+  plan_gemm(g1, part, plan);
   GemmSpec g2;
   g2.A = Hf; g2.B[0] = a.W2; g2.b_nk = 0; g2.C[0] = a.x; g2.resid = (const float*)a.x; g2.resid_add = true;
   g2.lda = a.F; g2.ldb = a.D; g2.ldc = a.D; g2.ldr = a.D;
   g2.M = T; g2.N = a.D; g2.K = a.F;
-  g2.c_dtype = PARTIR_F32; g2.rm = a.Rb; g2.rk = a.Rm; g2.tail_ok = true;
+  g2.c_dtype = PARTIR_F32; g2.rm = a.Rb; g2.rk = a.Rm; g2.tail_ok = g2.split_ok = true;
   g2.name = "mlp.down";
   g2.label = "dec.ffn_down x += sum_m H[:, m] . slice 0 W2[m]";
   plan_gemm(g2, part, plan);
@@ -997,9 +1090,9 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
   GemmSpec ga;
   ga.A = a.dY; ga.B[0] = a.Wo; ga.C[0] = dA;
   ga.lda = D; ga.ldb = D; ga.ldc = D; ga.M = T; ga.N = D; ga.K = D;
-  ga.c_dtype = PARTIR_BF16; ga.rm = a.Rb; ga.rn = a.Rm;
+  ga.c_dtype = PARTIR_BF16; ga.rm = a.Rb; ga.rn = a.Rm; ga.tail_ok = ga.split_ok = true;
   ga.name = "attn.bwd.da"; ga.label = "bwd.da dA = slice 0 dY[b] . (slice 0 Wo[m])^T";
-  plan_gemm(ga, nullptr, plan);
+  plan_gemm(ga, part, plan);
   AttnBwdArgs c;
   c.Q = Q; c.K = K; c.V = V; c.O = Ao; c.dO = dA; c.lse = lse;
   c.dQ = dQKV; c.dK = dQKV ? (char*)dQKV + D * 2 : nullptr; c.dV = dQKV ? (char*)dQKV + 2 * D * 2 : nullptr;
@@ -1015,7 +1108,7 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
   GemmSpec gx;
   gx.A = dQKV; gx.C[0] = a.dX;
   gx.lda = 3 * D; gx.ldb = D; gx.ldc = D; gx.M = T; gx.N = D; gx.K = 3 * D;
-  gx.c_dtype = PARTIR_F32; gx.rm = a.Rb;
+  gx.c_dtype = PARTIR_F32; gx.rm = a.Rb; gx.tail_ok = true;
   gx.name = "attn.bwd.dx"; gx.label = "bwd.dx dX = sum over m and q|k|v of dQKV[b][:, m] . W{q,k,v}[:, m]^T";
   {
     const size_t first = plan.launches.size();
@@ -1034,23 +1127,24 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
                            "bwd.dwk dWk = sum_b (slice 0 X[b])^T . dK[b][:, m]",
                            "bwd.dwv dWv = sum_b (slice 0 X[b])^T . dV[b][:, m]"};
   void* dW[3] = {a.dWq, a.dWk, a.dWv};
+  GemmSpec gw;
   for (int i = 0; i < 3; ++i) {
-    GemmSpec gw;
     gw.A = a.X; gw.a_mn = true;
     gw.B[0] = dQKV ? (char*)dQKV + i * D * 2 : nullptr; gw.b_nk = 0; gw.C[0] = dW[i];
     gw.lda = D; gw.ldb = 3 * D; gw.ldc = D; gw.M = D; gw.N = D; gw.K = T;
     gw.c_dtype = PARTIR_F32; gw.rn = a.Rm; gw.rk = a.Rb; gw.sum_impl = PARTIR_SUM_FUSED;
+    gw.tail_ok = gw.split_ok = true;
     gw.name = "attn.bwd.dwqkv"; gw.label = wnames[i];
-    plan_gemm(gw, nullptr, plan);
+    plan_gemm(gw, part, plan);
   }
   GemmSpec go;
   go.A = Ao; go.a_mn = true; go.B[0] = a.dY; go.b_nk = 0; go.C[0] = a.dWo;
   go.lda = D; go.ldb = D; go.ldc = D; go.M = D; go.N = D; go.K = T;
-  go.c_dtype = PARTIR_F32; go.rm = a.Rm; go.rk = a.Rb;
+  go.c_dtype = PARTIR_F32; go.rm = a.Rm; go.rk = a.Rb; go.tail_ok = go.split_ok = true;
   go.name = "attn.bwd.dwo"; go.label = "bwd.dwo dWo = sum_b A[b][:, m]^T . slice 0 dY[b]";
   plan_gemm(go, part, plan);
   plan.n_sum_loops = 4;
-  plan.ws_bytes = off + std::max(gemm_ws_bytes(gx), gemm_ws_bytes(go));
+  plan.ws_bytes = off + std::max({gemm_ws_bytes(ga), gemm_ws_bytes(gx), gemm_ws_bytes(gw), gemm_ws_bytes(go)});
 }
 
 // ---------------------------------------------------------------------------
@@ -1142,15 +1236,15 @@ void plan_mlp_bwd(const MlpBwdArgs& a, void* ws, Plan& plan) {
     if (!a.Z) {
       gz.A = a.X; gz.B[0] = a.W1; gz.b_nk = 0; gz.C[0] = Z; gz.bias[0] = (const float*)a.b1;
       gz.lda = D; gz.ldb = F; gz.ldc = F; gz.M = T; gz.N = F; gz.K = D;
-      gz.c_dtype = PARTIR_BF16; gz.rm = a.Rb; gz.rn = a.Rm;
+      gz.c_dtype = PARTIR_BF16; gz.rm = a.Rb; gz.rn = a.Rm; gz.tail_ok = true;
       gz.name = "mlp.bwd.z"; gz.label = "bwd.z  Z = slice 0 X[b] . slice 1 W1[m] (recomputed)";
-      plan_gemm(gz, nullptr, plan);
+      plan_gemm(gz, part, plan);
     }
     gh.A = a.dY; gh.B[0] = a.W2; gh.C[0] = dH;
     gh.lda = D; gh.ldb = D; gh.ldc = F; gh.M = T; gh.N = F; gh.K = D;
-    gh.c_dtype = PARTIR_BF16; gh.rm = a.Rb; gh.rn = a.Rm;
+    gh.c_dtype = PARTIR_BF16; gh.rm = a.Rb; gh.rn = a.Rm; gh.tail_ok = gh.split_ok = true;
     gh.name = "mlp.bwd.dh"; gh.label = "bwd.dh dH = slice 0 dY[b] . (slice 0 W2[m])^T";
-    plan_gemm(gh, nullptr, plan);
+    plan_gemm(gh, part, plan);
     Launch E;
     E.kind = L_ACT_BWD;
     E.name = "mlp.bwd.act";
@@ -1163,16 +1257,17 @@ void plan_mlp_bwd(const MlpBwdArgs& a, void* ws, Plan& plan) {
     g2.A = H; g2.a_mn = true; g2.B[0] = a.dY; g2.b_nk = 0; g2.C[0] = a.dW2;
     g2.lda = F; g2.ldb = D; g2.ldc = D; g2.M = F; g2.N = D; g2.K = T;
     g2.ab_dtype = PARTIR_BF16; g2.c_dtype = PARTIR_F32; g2.rm = a.Rm; g2.rk = a.Rb;
+    g2.tail_ok = g2.split_ok = true;
     g2.name = "mlp.bwd.dw2"; g2.label = "bwd.dw2 dW2 = sum_b H[b][:, m]^T . slice 0 dY[b]";
     plan_gemm(g2, part, plan);
     g1.A = a.X; g1.a_mn = true; g1.B[0] = dZ; g1.b_nk = 0; g1.C[0] = a.dW1;
     g1.lda = D; g1.ldb = F; g1.ldc = F; g1.M = D; g1.N = F; g1.K = T;
-    g1.c_dtype = PARTIR_F32; g1.rn = a.Rm; g1.rk = a.Rb;
+    g1.c_dtype = PARTIR_F32; g1.rn = a.Rm; g1.rk = a.Rb; g1.tail_ok = g1.split_ok = true;
     g1.name = "mlp.bwd.dw1"; g1.label = "bwd.dw1 dW1 = sum_b (slice 0 X[b])^T . dZ[b][:, m]";
     plan_gemm(g1, part, plan);
     gx.A = dZ; gx.B[0] = a.W1; gx.C[0] = a.dX;
     gx.lda = F; gx.ldb = F; gx.ldc = D; gx.M = T; gx.N = D; gx.K = F;
-    gx.c_dtype = PARTIR_F32; gx.rm = a.Rb; gx.rk = a.Rm;
+    gx.c_dtype = PARTIR_F32; gx.rm = a.Rb; gx.rk = a.Rm; gx.tail_ok = gx.split_ok = true;
     gx.name = "mlp.bwd.dx"; gx.label = "bwd.dx dX = sum_m dZ[b][:, m] . (slice 1 W1[m])^T";
     plan_gemm(gx, part, plan);
     plan.n_sum_loops = 3;
@@ -1191,7 +1286,10 @@ void plan_mlp_bwd(const MlpBwdArgs& a, void* ws, Plan& plan) {
     if (a.db2 && D > 0) plan_colsum(a.dY, csp, a.db2, T, D, false, "mlp.bwd.db", plan);
   }
   size_t gws = 0;
-  if (live) gws = std::max({gemm_ws_bytes(g2), gemm_ws_bytes(g1), gemm_ws_bytes(gx)});
+  if (live) {
+    gws = std::max({gemm_ws_bytes(gh), gemm_ws_bytes(g2), gemm_ws_bytes(g1), gemm_ws_bytes(gx)});
+    if (!a.Z) gws = std::max(gws, gemm_ws_bytes(gz));
+  }
   plan.ws_bytes = off + gws;
 }
 
@@ -1258,7 +1356,7 @@ size_t partir_loop_matmul_workspace(int64_t M, int64_t N, int64_t K, int ab_dtyp
   a.ldb = b_layout == PARTIR_B_KN ? ((N + 7) / 8) * 8 : a.lda;
   a.ldc = ((N + 7) / 8) * 8;
   if (validate_matmul(a, false) != PARTIR_OK) return (size_t)-1;
-  return gemm_ws_bytes(matmul_spec(a));
+  return matmul_ws_bytes(matmul_spec(a));
 }
 
 int partir_plan_loop_matmul(int64_t M, int64_t N, int64_t K, int ab_dtype, int c_dtype, int b_layout,
