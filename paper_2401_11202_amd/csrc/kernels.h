@@ -97,10 +97,9 @@ struct GemmF32Params {
   int64_t lda, ldb, ldc, part_stride;
   int M, N, K;
   int b_nk;
-  int rm, ms, tpm;
-  int rn, ns, tpn;
-  int rk, ks;
+  int tile;          // output tile edge: 128 or 64 (64 with a leading dim above 2^24)
   int tiles_m, tiles_n;
+  int ks;            // K extent of a part
   int nsplit;
   int epi;           // EPI_F32 or EPI_PARTIAL
 };

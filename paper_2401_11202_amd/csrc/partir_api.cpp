@@ -229,6 +229,18 @@ GemmTiling gemm_tiling(const GemmSpec& g) {
   return best;
 }
 
+// Output tile of an fp32 product.  Per 32-wide K tile a CU takes 1.95 us for a
+// 128-wide tile and 0.55 us for a 64-wide one (measured: 4096^3 955 / 1009 us,
+// 1800 x 2056 x 2048 134 / 150, 2900^3 514 / 431, 333 x 2500 x 3000 180 / 57):
+// the larger tile wherever its whole waves are not mostly idle.
+int gemm_f32_tiling(const GemmSpec& g, int nsplit) {
+  constexpr int64_t kMaxLd = (int64_t)1 << 24;   // the tiles' loads are bounded by 32-bit byte ranges
+  if (g.lda > kMaxLd || g.ldb > kMaxLd) return 64;
+  const double n64 = std::max(1.0, (double)(gemm_tiles(g, 64) * nsplit) / kNumCU);
+  const int64_t n128 = cdiv(gemm_tiles(g, 128) * nsplit, kNumCU);
+  return 1.95 * n128 <= 0.55 * n64 ? 128 : 64;
+}
+
 // Workspace of one GEMM: split-K partials, or the tail parts of 256-wide tiles.
 size_t gemm_ws_bytes(const GemmSpec& g) {
   if (g.ab_dtype != PARTIR_BF16)
@@ -334,7 +346,7 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
       return 2;
     }
   } else {
-    const int tile = gemm_f32_tile();
+    const int tile = gemm_f32_tiling(g, nparts);
     GemmF32Params& p = L.gemm32;
     p.A = (const float*)g.A;
     p.B = (const float*)g.B[0];
@@ -343,15 +355,15 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     p.ldc = split ? g.N : g.ldc;
     p.part_stride = g.M * g.N;
     p.M = (int)g.M; p.N = (int)g.N; p.K = (int)g.K; p.b_nk = g.b_nk;
-    p.rm = g.rm; p.ms = (int)(g.M / g.rm); p.tpm = (int)cdiv(p.ms, tile);
-    p.rn = g.rn; p.ns = (int)(g.N / g.rn); p.tpn = (int)cdiv(p.ns, tile);
-    p.rk = g.rk; p.ks = (int)(g.K / g.rk);
-    p.tiles_m = p.rm * p.tpm; p.tiles_n = p.rn * p.tpn;
+    p.tile = tile;
+    p.ks = (int)(g.K / g.rk);
+    p.tiles_m = (int)cdiv(g.M, tile); p.tiles_n = (int)cdiv(g.N, tile);
     p.nsplit = split ? g.rk : 1;
     p.epi = split ? EPI_PARTIAL : EPI_F32;
     L.kind = L_GEMM_F32;
     L.name = g.name;
-    L.text = describe_gemm(g, (int64_t)p.tiles_m * p.tiles_n * p.nsplit, split);
+    L.text = describe_gemm(g, (int64_t)p.tiles_m * p.tiles_n * p.nsplit, split) +
+             "; workgroup tiles of " + std::to_string(tile);
   }
   plan.launches.push_back(L);
   if (split) {
