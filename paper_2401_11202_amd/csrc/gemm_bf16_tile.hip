@@ -7,22 +7,27 @@
 // (16x16x32, K ascending in steps of 32) forms every sum, so an output element
 // whose K range is not split has the same bits whichever tile computed it.
 //
-// Four waves (2 x 2) own a quarter of the tile each.  K advances in 64-wide
-// tiles through NS LDS stages filled by direct-to-LDS buffer loads; one
-// barrier per K tile, in its middle:
+// 2 x WN waves own equal parts of the tile.  K advances in 64-wide tiles
+// through NS LDS stages filled by direct-to-LDS buffer loads; one barrier per
+// K tile, in its middle:
 //   step 0   MFMAs of k 0..31,  fragments of k 32..63 read meanwhile
 //   wait     tile kt+1 landed (the younger loads stay in flight), barrier
 //   refill   this stage with tile kt+NS (every wave has read all of it)
 //   step 1   MFMAs of k 32..63, first fragments of tile kt+1 read meanwhile
-// so between NS - 1 and NS tiles are in flight.  A short grid is bound by
-// the latency of this chain and by the bytes in flight, not by the MFMAs:
-// four stages (one workgroup a CU, 128 KiB) while the grid has at most one
-// 128-wide tile a CU, two (two workgroups a CU) above.  On full CUs the LDS
-// bounds the 128-wide tile: 96 KiB read and written per K tile for 512 cycles
-// of MFMAs.  Measured against 256-wide tiles (launch time, us): 2048^3 44 -> 24,
-// 200 x 16384 x 4096 57 -> 41, 200 x 4096 x 16384 108 -> 44 (with 4 K parts),
-// 512 x 1024 x 256 13 -> 7 (64-wide); on whole waves the 256-wide tile is the
-// better one (4096^3: 95 against 118).
+// so between NS - 1 and NS tiles are in flight.
+//
+// The 128-wide tile has two forms.  A grid of at most one workgroup a CU is
+// bound by the latency of this chain and by the bytes in flight: four stages
+// (128 KiB) and eight waves, so that a SIMD has a second wave to run while one
+// waits for its fragments (2048^3 24.4 us with four waves, 21.7 with eight;
+// 200 x 16384 x 4096 39.4 and 36.0).  A larger grid runs two workgroups of
+// four waves a CU on two stages each (4096^3 119 us; with eight waves 122,
+// their smaller wave tiles read more LDS).  Per K tile (2048 x 2048 x 8192,
+// one workgroup a CU) the MFMAs alone take 0.29 us, with the fragment reads
+// 0.40, with the loads 0.52: LDS and L1 traffic per MFMA bound it, which is why
+// the 256-wide tile is better on whole waves (4096^3: 95 us).  Before / after
+// this kernel (launch time, us): 2048^3 44 -> 22, 200 x 16384 x 4096 57 -> 36,
+// 200 x 4096 x 16384 108 -> 42 (4 K parts), 512 x 1024 x 256 13 -> 7 (64-wide).
 #include <type_traits>
 
 #include "kernels.h"
@@ -41,7 +46,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 64, NT = 256;
+constexpr int BK = 64;
 constexpr uint32_t OOB = 0x80000000u;          // offset that reads as zero
 
 template <typename T>
@@ -66,23 +71,24 @@ __device__ __forceinline__ int mn_swz(int r) {
 // other stages).
 __device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { return *(const bf16x8*)p; }
 
-template <int BM, int BN, int NS, int AMN, int BMN, int PARTS>
+template <int BM, int BN, int WN, int NS, int AMN, int BMN, int PARTS>
 __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* t) {
   static_assert(!(PARTS && (AMN || BMN)), "device-local arrays are K-contiguous");
-  constexpr int WTM = BM / 2, WTN = BN / 2;        // a wave's part of the tile
+  constexpr int NW = 2 * WN;                       // waves, 2 x WN
+  constexpr int WTM = BM / 2, WTN = BN / WN;       // a wave's part of the tile
   constexpr int MI = WTM / 16, NJ = WTN / 16;
   constexpr int OPA = BM * BK * 2, OPB = BN * BK * 2, STAGE = OPA + OPB;
-  constexpr int LA = BM / 32, LB = BN / 32;        // wave loads (1 KiB) per wave per K tile
+  constexpr int LA = BM / (8 * NW), LB = BN / (8 * NW);        // wave loads (1 KiB) per wave per K tile
   constexpr int LPS = LA + LB;
   // epilogue staging: 16 rows of the wave's columns, fp32, padded
   constexpr int CP = WTN + 4;
   constexpr int CW = 16 * CP * 4;
-  static_assert(4 * 2 * CW <= NS * STAGE, "epilogue staging fits the K stages");
+  static_assert(NW * 2 * CW <= NS * STAGE, "epilogue staging fits the K stages");
   __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / WN, wn = wave % WN;
 
   // ---- which tile -----------------------------------------------------------
   // XCD x (workgroups go round-robin to the 8 XCDs) takes a contiguous run of
@@ -112,14 +118,14 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
   const int nk = (k_end - k_begin + BK - 1) / BK;
 
   // ---- global -> LDS loads ----------------------------------------------------
-  // K-contiguous operand: load j of wave w fills tile rows 32 j + 8 w .. +7;
+  // K-contiguous operand: load j of wave w fills tile rows 8 (NW j + w) .. +7;
   // lane L takes row +L/8 and LDS chunk L%8 = global chunk (L%8) ^ swz(row).
-  // One descriptor per 32 rows bounds the valid rows (rows past it read zero).
-  // MN-major operand: load j of wave w fills R = 512 / W k rows at R (4 j + w);
+  // One descriptor per 64 rows bounds the valid rows (rows past it read zero).
+  // MN-major operand: load j of wave w fills R = 512 / W k rows at R (NW j + w);
   // a descriptor per K tile bounds the k rows at the end of K and the last one
   // at the operand's last column.
   const uint16_t* Bg = pick3(grp, p.B[0], p.B[1], p.B[2]);
-  __amdgpu_buffer_rsrc_t ra[LA], rb[LB];
+  __amdgpu_buffer_rsrc_t ra[BM / 64], rb[BN / 64];
   auto b_ptr = [&](int r0, int kp) -> const uint16_t* {
     if (PARTS && t->b_nrows) {
       const int gb = grp * t->b_gstride;
@@ -131,42 +137,58 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
   };
   auto b_desc = [&](int kp) {
 #pragma unroll
-    for (int j = 0; j < LB; ++j)
-      rb[j] = make_rsrc(b_ptr(32 * j, kp), (uint32_t)(min(max(cols - 32 * j, 0), 32) * p.ldb * 2));
+    for (int j = 0; j < BN / 64; ++j)
+      rb[j] = make_rsrc(b_ptr(64 * j, kp), (uint32_t)(min(max(cols - 64 * j, 0), 64) * p.ldb * 2));
   };
   if (!AMN) {
 #pragma unroll
-    for (int j = 0; j < LA; ++j) {
-      const uint16_t* a = p.A + (int64_t)(row0 + 32 * j) * p.lda;
+    for (int j = 0; j < BM / 64; ++j) {
+      const uint16_t* a = p.A + (int64_t)(row0 + 64 * j) * p.lda;
       if (PARTS && t->a_rows) {
-        const int r = row0 + (32 * j < rows ? 32 * j : 0);
+        const int r = row0 + (64 * j < rows ? 64 * j : 0);
         const int ab = r / t->a_rows;
         a = t->a[ab] + (int64_t)(r - ab * t->a_rows) * p.lda;
       }
-      ra[j] = make_rsrc(a, (uint32_t)(min(max(rows - 32 * j, 0), 32) * p.lda * 2));
+      ra[j] = make_rsrc(a, (uint32_t)(min(max(rows - 64 * j, 0), 64) * p.lda * 2));
     }
   }
   if (!BMN) b_desc(0);
-  int b_kpart = 0;
-  int b_kend = (PARTS && t->b_nrows) ? t->b_kcols : 0;
+  // the all_gather of B along K: the part that holds K tile kt (a K tile never
+  // spans two, and they come in order)
+  int b_kpart = 0, b_k0 = 0;
+  auto b_advance = [&](int kt) {
+    if (PARTS && t->b_nrows) {
+      const int kb = k_begin + kt * BK;
+      while (kb >= b_k0 + t->b_kcols && b_kpart + 1 < t->b_nk) {
+        ++b_kpart;
+        b_k0 += t->b_kcols;
+        b_desc(b_kpart);
+      }
+    }
+  };
   const int lrow = 8 * wave + (lane >> 3);
   const int lchunk = (lane & 7) ^ swz(lrow);
-  const uint32_t a_voff = (uint32_t)(lrow * p.lda * 2 + lchunk * 16);
-  const uint32_t b_voff = (uint32_t)(lrow * p.ldb * 2 + lchunk * 16);
+  constexpr int RL = 8 * NW, LPB = 64 / RL;   // rows per load of all waves, loads per 64 rows
+  uint32_t a_voff[LPB], b_voff[LPB];
+#pragma unroll
+  for (int e = 0; e < LPB; ++e) {
+    a_voff[e] = (uint32_t)((lrow + RL * e) * p.lda * 2 + lchunk * 16);
+    b_voff[e] = (uint32_t)((lrow + RL * e) * p.ldb * 2 + lchunk * 16);
+  }
   uint32_t a_mv[LA], b_mv[LB];
   if (AMN) {
     constexpr int R = 512 / BM;
     const int r0 = R * wave + lane / (BM / 8);
 #pragma unroll
     for (int j = 0; j < LA; ++j)
-      a_mv[j] = (uint32_t)((4 * R * j + r0) * p.lda * 2 + (((lane % (BM / 8)) ^ mn_swz<BM>(r0)) << 4));
+      a_mv[j] = (uint32_t)((NW * R * j + r0) * p.lda * 2 + (((lane % (BM / 8)) ^ mn_swz<BM>(r0)) << 4));
   }
   if (BMN) {
     constexpr int R = 512 / BN;
     const int r0 = R * wave + lane / (BN / 8);
 #pragma unroll
     for (int j = 0; j < LB; ++j)
-      b_mv[j] = (uint32_t)((4 * R * j + r0) * p.ldb * 2 + (((lane % (BN / 8)) ^ mn_swz<BN>(r0)) << 4));
+      b_mv[j] = (uint32_t)((NW * R * j + r0) * p.ldb * 2 + (((lane % (BN / 8)) ^ mn_swz<BN>(r0)) << 4));
   }
   // what the last k row of an MN-major operand lacks of a whole leading dim
   const uint32_t a_cut = (uint32_t)(p.lda - (p.M - row0)) * 2, b_cut = (uint32_t)(p.ldb - (p.N - col0)) * 2;
@@ -184,33 +206,23 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
       const __amdgpu_buffer_rsrc_t r = make_rsrc(p.A + (int64_t)kb * p.lda + row0, bytes);
 #pragma unroll
       for (int j = 0; j < LA; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(la + j * 4096), 16, a_mv[j], 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(la + j * NW * 1024), 16, a_mv[j], 0, 0, 0);
     } else {
 #pragma unroll
       for (int j = 0; j < LA; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra[j], (lds_void*)(la + j * 4096), 16, a_voff | kmask, so, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra[j / LPB], (lds_void*)(la + j * NW * 1024), 16, a_voff[j % LPB] | kmask, so, 0, 0);
     }
     if constexpr (BMN) {
       const uint32_t bytes = kvalid * (uint32_t)p.ldb * 2 - (kvalid ? b_cut : 0u);
       const __amdgpu_buffer_rsrc_t r = make_rsrc(Bg + (int64_t)kb * p.ldb + col0, bytes);
 #pragma unroll
       for (int j = 0; j < LB; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(lb + j * 4096), 16, b_mv[j], 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(lb + j * NW * 1024), 16, b_mv[j], 0, 0, 0);
     } else {
-      uint32_t so_b = so;
-      if (PARTS && t->b_nrows) {   // the all_gather of B along K: a K tile never straddles a part
-        if (kb >= b_kend && b_kpart + 1 < t->b_nk) {
-          while (kb >= b_kend && b_kpart + 1 < t->b_nk) {
-            ++b_kpart;
-            b_kend += t->b_kcols;
-          }
-          b_desc(b_kpart);
-        }
-        so_b = (uint32_t)(kb - (b_kend - t->b_kcols)) * 2;
-      }
+      const uint32_t so_b = PARTS ? (uint32_t)(kb - b_k0) * 2 : so;
 #pragma unroll
       for (int j = 0; j < LB; ++j)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb[j], (lds_void*)(lb + j * 4096), 16, b_voff | kmask, so_b, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb[j / LPB], (lds_void*)(lb + j * NW * 1024), 16, b_voff[j % LPB] | kmask, so_b, 0, 0);
     }
   };
 
@@ -272,12 +284,16 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
   }
   bf16x8 fa0[MI], fb0[NJ], fa1[MI], fb1[NJ];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) gload(s, s);
+  for (int s = 0; s < NS; ++s) {
+    b_advance(s);
+    gload(s, s);
+  }
   WAIT_VMCNT(LPS * (NS - 1));
   barrier();
   ldfrag(0, 0, fa0, fb0);
   int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
+    b_advance(kt + NS);
     ldfrag(st, 1, fa1, fb1);
     mma(fa0, fb0);
     SLOTS(false);
@@ -342,6 +358,11 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const float* c = put(i, apply_act);
+      uint16_t* ob = out + (int64_t)(row0 + wr0 + i * 16) * p.ldc;
+      if (PARTS && parted) {   // the 16 rows share a part (c_rows % 16 == 0): one scalar table read
+        const int r = row0 + wr0 + i * 16, cb = min(r, p.M - 1) / t->c_rows;
+        ob = (uint16_t*)t->c[cb] + (int64_t)(r - cb * t->c_rows) * p.ldc;
+      }
 #pragma unroll
       for (int r0 = 0; r0 < 16; r0 += RPP) {
         const f32x4 lo = *(const f32x4*)(c + (r0 + cr) * CP + cc), hi = *(const f32x4*)(c + (r0 + cr) * CP + cc + 4);
@@ -349,14 +370,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
         if (rl >= rows || cl >= cols) continue;
         const bf16x8 o = {(__bf16)lo[0], (__bf16)lo[1], (__bf16)lo[2], (__bf16)lo[3],
                           (__bf16)hi[0], (__bf16)hi[1], (__bf16)hi[2], (__bf16)hi[3]};
-        int64_t grow = row0 + rl;
-        uint16_t* ob = out;
-        if (PARTS && parted) {
-          const int cb = (int)grow / t->c_rows;
-          ob = (uint16_t*)t->c[cb];
-          grow -= (int64_t)cb * t->c_rows;
-        }
-        uint16_t* dst = ob + grow * p.ldc + col0 + cl;
+        uint16_t* dst = ob + (int64_t)(r0 + cr) * p.ldc + col0 + cl;
         const i32x4 v = __builtin_bit_cast(i32x4, o);
         if (cl + 8 <= cols) *(i32x4*)dst = v;
         else *(int2*)dst = make_int2(v[0], v[1]);   // a 4-column tail (cols % 8 == 4)
@@ -374,65 +388,71 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
   float* out = epi == EPI_PARTIAL ? p.partial + split * p.part_stride : (float*)Cg;
   const int64_t ldo = epi == EPI_PARTIAL ? p.part_ld : p.ldc;
   const bool parted = PARTS && epi != EPI_PARTIAL && t->c_rows;
-  auto dst_of = [&](int rl) -> float* {
-    int64_t grow = row0 + rl;
-    float* ob = out;
+  // start of the 16 rows of block i (which share a part: one scalar table read)
+  auto rows_of = [&](int i) -> float* {
+    const int r = row0 + wr0 + i * 16;
     if (parted) {
-      const int cb = (int)grow / t->c_rows;
-      ob = (float*)t->c[cb];
-      grow -= (int64_t)cb * t->c_rows;
+      const int cb = min(r, p.M - 1) / t->c_rows;
+      return (float*)t->c[cb] + (int64_t)(r - cb * t->c_rows) * ldo;
     }
-    return ob + grow * ldo + col0 + wc0 + cc;
+    return out + (int64_t)r * ldo;
   };
   // a residual (which may alias C: each element is read, then written, by
   // the same lane) is read before the rows are staged: one round trip
   f32x4 rv[MI][NP];
   if (epi == EPI_RESID_F32) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i) {
+      const float* src = parted ? rows_of(i) : p.resid + (int64_t)(row0 + wr0 + i * 16) * p.ldr;
+      const int64_t lds = parted ? ldo : p.ldr;
 #pragma unroll
       for (int k = 0; k < NP; ++k) {
         const int rl = wr0 + i * 16 + k * RPP + cr;
         rv[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         if (rl < rows && wc0 + cc < cols)
-          rv[i][k] = *(const f32x4*)(parted ? dst_of(rl) : p.resid + (int64_t)(row0 + rl) * p.ldr + col0 + wc0 + cc);
+          rv[i][k] = *(const f32x4*)(src + (k * RPP + cr) * lds + col0 + wc0 + cc);
       }
+    }
   }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const float* c = put(i, act != 0);
+    float* dst = rows_of(i) + col0 + wc0 + cc;
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
       const int rl = wr0 + i * 16 + k * RPP + cr;
       f32x4 v = *(const f32x4*)(c + (k * RPP + cr) * CP + cc);
       if (rl >= rows || wc0 + cc >= cols) continue;
       if (epi == EPI_RESID_F32) v = rv[i][k] + v;
-      *(f32x4*)dst_of(rl) = v;
+      *(f32x4*)(dst + (k * RPP + cr) * ldo) = v;
     }
     wave_sync();
   }
 }
 
-// workgroups per CU by LDS (one wave of each per SIMD)
-constexpr int wgs_per_cu(int bm, int bn, int ns) { return 160 * 1024 / (ns * (bm + bn) * BK * 2); }
-
-template <int BM, int BN, int NS, int AMN, int BMN>
-__global__ __launch_bounds__(NT, wgs_per_cu(BM, BN, NS)) void gemm_bf16_tile_kernel(GemmParams p) {
-  tile_body<BM, BN, NS, AMN, BMN, 0>(p, nullptr);
+// waves per SIMD by LDS
+constexpr int waves_per_simd(int bm, int bn, int wn, int ns) {
+  return 160 * 1024 / (ns * (bm + bn) * BK * 2) * 2 * wn / 4;
 }
 
-template <int BM, int BN, int NS>
-__global__ __launch_bounds__(NT, wgs_per_cu(BM, BN, NS)) void gemm_bf16_tile_parts_kernel(GemmParams p, GemmParts t) {
-  tile_body<BM, BN, NS, 0, 0, 1>(p, &t);
+template <int BM, int BN, int WN, int NS, int AMN, int BMN>
+__global__ __launch_bounds__(128 * WN, waves_per_simd(BM, BN, WN, NS)) void gemm_bf16_tile_kernel(GemmParams p) {
+  tile_body<BM, BN, WN, NS, AMN, BMN, 0>(p, nullptr);
 }
 
-template <int BM, int BN, int NS>
+template <int BM, int BN, int WN, int NS>
+__global__ __launch_bounds__(128 * WN, waves_per_simd(BM, BN, WN, NS))
+void gemm_bf16_tile_parts_kernel(GemmParams p, GemmParts t) {
+  tile_body<BM, BN, WN, NS, 0, 0, 1>(p, &t);
+}
+
+template <int BM, int BN, int WN, int NS>
 hipError_t launch(const GemmParams& p, const GemmParts* t, hipStream_t s) {
-  const dim3 grid((unsigned)((int64_t)p.tiles_m * p.tiles_n * p.nsplit)), block(NT);
-  if (t) hipLaunchKernelGGL((gemm_bf16_tile_parts_kernel<BM, BN, NS>), grid, block, 0, s, p, *t);
-  else if (p.a_mn && p.b_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, NS, 1, 1>), grid, block, 0, s, p);
-  else if (p.b_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, NS, 0, 1>), grid, block, 0, s, p);
-  else if (!p.a_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, NS, 0, 0>), grid, block, 0, s, p);
+  const dim3 grid((unsigned)((int64_t)p.tiles_m * p.tiles_n * p.nsplit)), block(128 * WN);
+  if (t) hipLaunchKernelGGL((gemm_bf16_tile_parts_kernel<BM, BN, WN, NS>), grid, block, 0, s, p, *t);
+  else if (p.a_mn && p.b_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, WN, NS, 1, 1>), grid, block, 0, s, p);
+  else if (p.b_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, WN, NS, 0, 1>), grid, block, 0, s, p);
+  else if (!p.a_mn) hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, WN, NS, 0, 0>), grid, block, 0, s, p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -448,8 +468,8 @@ hipError_t launch_gemm_bf16_tile(const GemmParams& p, const GemmParts* t, hipStr
                             (int64_t)(p.ngroups - 1) * t->b_gstride +
                                     (int64_t)((p.N + t->b_nrows - 1) / t->b_nrows) * t->b_nk > kMaxParts))))
     return hipErrorInvalidValue;
-  if (p.tile == 128) return nwg > 256 ? launch<128, 128, 2>(p, t, s) : launch<128, 128, 4>(p, t, s);
-  if (p.tile == 64) return launch<64, 64, 4>(p, t, s);
+  if (p.tile == 128) return nwg > 256 ? launch<128, 128, 2, 2>(p, t, s) : launch<128, 128, 4, 4>(p, t, s);
+  if (p.tile == 64) return launch<64, 64, 2, 4>(p, t, s);
   return hipErrorInvalidValue;
 }
 

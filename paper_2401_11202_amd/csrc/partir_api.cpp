@@ -180,10 +180,11 @@ struct GemmTiling {
 
 // Time of a bf16 product in microseconds, from the tiles a CU runs one after
 // the other (n) and the 64-wide K tiles of each (nk).  The constants are
-// fitted to measurements (MI355X, B as [N, K] and [K, N], time of the launch):
-//   tile 256  1 x 64: 95, 1 x 40: 62, 2 x 24: 89     one workgroup per CU
-//   tile 128  1 x 32: 24, 1 x 64: 43, 1 x 128: 78, 3 x 32: 50, 4 x 64: 120
-//   tile 64   1 x 16: 10, 1 x 256: 73, 4 x 32: 33    n > 1: up to two at a time
+// fitted to measurements (n x nk: us of the launch):
+//   tile 256  1 x 64: 95, 1 x 40: 62, 1 x 32: 53, 2 x 24: 89   one workgroup a CU
+//   tile 128  1 x 32: 22, 1 x 64: 36, 1 x 128: 72, 3 x 32: 54, 4 x 64: 119
+//             (two at a time; an odd last one alone)
+//   tile 64   1 x 16: 10, 1 x 256: 73, 4 x 32: 33
 // A 256 tile does the most work per byte moved through LDS (1450 TFLOP/s on
 // full waves against 1200 and 700), so the small tiles pay where its grid
 // leaves CUs idle.  A K split adds the partials' traffic and a launch.
@@ -195,7 +196,7 @@ double gemm_us(const GemmSpec& g, int tile, int parts) {
   int64_t base;
   const int tail = tile == 256 && parts == 1 ? gemm_tail_parts(g, &base) : 1;
   if (tile == 256) t = 3 + (tail > 1 ? n - 1 + 1.0 / tail : n) * (6 + 1.38 * nk) + (tail > 1 ? 5 + 10 * tail : 0);
-  else if (tile == 128) t = 5 + (n == 1 ? 0.55 * nk : n * (1 + 0.42 * nk));
+  else if (tile == 128) t = 5 + std::floor(n / 2) * (2 + 0.87 * nk) + (std::fmod(n, 2) > 0 ? 1 + 0.52 * nk : 0);
   else t = 5 + std::max(0.27 * nk, n * (0.5 + 0.2 * nk));
   if (parts > 1) t += 5 + 8.0 * parts * g.M * g.N / 5.5e6;   // 5.5 MB/us, written and read
   return t;

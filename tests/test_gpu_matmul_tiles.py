@@ -24,8 +24,8 @@ def product(A, B, layout, out=torch.float32, **kw):
 # several tiles, K shorter than the LDS pipeline, one and many workgroups a CU
 @pytest.mark.parametrize("layout", ["kn", "nk"])
 @pytest.mark.parametrize("M,N,K,words", [
-    (1, 8, 8, "tiles of 128 x 128"),
-    (63, 56, 72, "tiles of 128 x 128"),
+    (1, 8, 8, "tiles of 64 x 64"),
+    (63, 56, 72, "tiles of 64 x 64"),
     (65, 72, 136, "tiles of 64 x 64"),
     (192, 264, 448, "tiles of 64 x 64"),
     (130, 4104, 200, "tiles of 64 x 64"),
