@@ -41,22 +41,37 @@ constexpr int RP = 256;
 // wait on the next tiles' DMA (which writes the other stage).
 __device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { return *(const bf16x8*)p; }
 
+// KG = 1: four waves, every one over all the workgroup's keys.
 // BKV = 32: three workgroups per CU (32 KiB of LDS each, at most 168
 // VGPRs); the third wave per SIMD hides more of the load, LDS and barrier
 // waits than the halved work between barriers costs.  BKV = 64: two per CU
 // (64 KiB), fewer barriers; the host takes it for grids smaller than the
 // CU count, where occupancy cannot help.
-template <int BKV>
-__global__ __launch_bounds__(NT, BKV == 32 ? 3 : 2)
+// KG = 2: eight waves in two groups that share the queries and split the keys,
+// group kg taking every other block of BKV = 64 through LDS stages of its own
+// (128 KiB in all); at the end the first group folds the second's (m, l, O) into
+// its own, the combiner of the key shards.  A grid of up to two workgroups a
+// CU is bound by its longest workgroups, whose waves are one chain of S^T,
+// exponentials and P V per block: two chains a SIMD overlap, and each is half
+// as long.  Measured (1 / 2 groups, launch): 8192 keys x 2 heads 147 / 108 us,
+// 4096 x 8 heads 87 / 62, 2048 x 20 heads 51 / 39, 1024 x 32 (sequence, head)s
+// 29 / 25.  Not below 512 keys (256 keys 12.8 / 13.4: the merge costs more) nor on
+// larger grids, where 32-key blocks at three workgroups a CU do better (3 x 2048
+// x 16: 81 either way).  More stages (loads three blocks ahead) changed nothing.
+template <int BKV, int KG>
+__global__ __launch_bounds__(NT * KG, KG == 1 && BKV == 32 ? 3 : 2)
 void attention_kernel(AttnParams p) {
   static_assert(BKV == 32 || BKV == 64, "key blocks of 32 or 64");
   constexpr int NSUB = BKV / 32;            // 32-key sub-tiles of S^T
   constexpr int T_BYTES = BKV * RP;
   constexpr int STAGE = 2 * T_BYTES;      // K tile, then V tile
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+  constexpr int MERGE = KG > 1 ? 4 * 64 * 66 * 4 : 0;   // O (64 per lane), m and l of the second key group
+  static_assert(KG * 2 * STAGE >= MERGE, "the merge reuses the stages");
+  __shared__ __attribute__((aligned(1024))) char smem[KG * 2 * STAGE];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so per-wave tests branch
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so per-wave tests branch
+  const int w = wave & 3, kg = KG > 1 ? wave >> 2 : 0;         // query quarter, key group
   const int h = lane >> 5, col = lane & 31;
 
   // heaviest (latest) query blocks first: causal work grows with the block
@@ -117,7 +132,7 @@ void attention_kernel(AttnParams p) {
   const uint32_t kstep = (uint32_t)(BKV * p.ldk * 2), vstep = (uint32_t)(BKV * p.ldv * 2);
   const uint32_t krow16 = (uint32_t)(16 * p.ldk * 2), vrow16 = (uint32_t)(16 * p.ldv * 2);
   auto gload = [&](int kb, int buf) {
-    char* ks = smem + buf * STAGE + w * 1024;
+    char* ks = smem + (kg * 2 + buf) * STAGE + w * 1024;
     char* vs = ks + T_BYTES;
 #pragma unroll
     for (int i = 0; i < BKV / 16; ++i) {
@@ -149,7 +164,7 @@ void attention_kernel(AttnParams p) {
   const int nkb = p.nsplit > 1 ? min(nkb_all, kb_begin + p.kb_per * (64 / BKV)) : nkb_all;   // one past the last block
   const int wave_last_q = q0 + 32 * w + 31;
 
-  if (kb_begin < nkb) gload(kb_begin, 0);
+  if (kb_begin + kg < nkb) gload(kb_begin + kg, 0);
   // Every load so far (the Q fragments included) has landed on every path
   // into the loop; without this the wait insertion cannot tell on the path
   // that skips the first block, and waits on the next block's prefetch
@@ -161,10 +176,10 @@ void attention_kernel(AttnParams p) {
   auto block = [&](auto stage_c, int kb) {
     constexpr int cur = decltype(stage_c)::value;
     // the other stage was finished with before the last barrier
-    if (kb + 1 < nkb) gload(kb + 1, cur ^ 1);
+    if (kb + KG < nkb) gload(kb + KG, cur ^ 1);
     const int k0 = kb * BKV;
-    if (!p.causal || k0 <= wave_last_q) {
-      const char* ks = smem + cur * STAGE;
+    if ((KG == 1 || kb < nkb) && (!p.causal || k0 <= wave_last_q)) {
+      const char* ks = smem + (kg * 2 + cur) * STAGE;
       const char* vs = ks + T_BYTES;
       // S^T = K Q^T for NSUB 32-key sub-tiles: this lane's column holds
       // query qi, keys k0 + 32 t + 8 (v / 4) + 4 h + v % 4 in element v of
@@ -263,12 +278,43 @@ void attention_kernel(AttnParams p) {
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads of the next tiles landed
     __syncthreads();
   };
-  for (int kb = kb_begin; kb < nkb; kb += 2) {
-    block(std::integral_constant<int, 0>{}, kb);
-    if (kb + 1 < nkb) block(std::integral_constant<int, 1>{}, kb + 1);
+  // key group kg takes blocks kb_begin + kg, + KG, ...; the trip count (and so
+  // every barrier) is the workgroup's
+  for (int kb = kb_begin; kb < nkb; kb += 2 * KG) {
+    block(std::integral_constant<int, 0>{}, kb + kg);
+    if (kb + KG < nkb) block(std::integral_constant<int, 1>{}, kb + KG + kg);
   }
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (KG > 1) {
+    // (m, l, O) (+) (m', l', O') of the two key groups, in that order; the
+    // stages are free (the loop ended on a barrier with no load in flight)
+    f32x4* const mo = (f32x4*)smem + (w * 64 + lane);
+    float2* const ml = (float2*)(smem + 4 * 64 * 64 * 4) + (w * 64 + lane);
+    if (kg == 1) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          mo[(4 * d + g) * 256] = f32x4{oacc[d][4 * g + 0], oacc[d][4 * g + 1], oacc[d][4 * g + 2], oacc[d][4 * g + 3]};
+      *ml = make_float2(m_run, l_tot);
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const float2 o = *ml;
+    const float m_new = fmaxf(m_run, o.x);   // a group without keys holds (-1e30, 0, 0)
+    const float a0 = __builtin_amdgcn_exp2f(m_run - m_new), a1 = __builtin_amdgcn_exp2f(o.x - m_new);
+    l_tot = a0 * l_tot + a1 * o.y;
+    m_run = m_new;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 v = mo[(4 * d + g) * 256];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[d][4 * g + e] = a0 * oacc[d][4 * g + e] + a1 * v[e];
+      }
+  }
   if (p.nsplit > 1) {
     // one shard of the key loop: unnormalised output and (m, l) for the combine
     const int64_t tq = tok0 + qi;
@@ -352,10 +398,14 @@ hipError_t launch_attention(const AttnParams& p, hipStream_t s) {
     }
     if (cus[dev] > 0) ncu = cus[dev];
   }
-  if (nwg < (unsigned)ncu)
-    hipLaunchKernelGGL(attention_kernel<64>, dim3(nwg), dim3(NT), 0, s, p);
+  // the bounds are those of the kernel's comment
+  const int keys = p.nsplit > 1 ? p.kb_per * 64 : p.S;
+  if (keys >= 512 && nwg <= 2 * (unsigned)ncu)
+    hipLaunchKernelGGL((attention_kernel<64, 2>), dim3(nwg), dim3(2 * NT), 0, s, p);
+  else if (nwg < (unsigned)ncu)
+    hipLaunchKernelGGL((attention_kernel<64, 1>), dim3(nwg), dim3(NT), 0, s, p);
   else
-    hipLaunchKernelGGL(attention_kernel<32>, dim3(nwg), dim3(NT), 0, s, p);
+    hipLaunchKernelGGL((attention_kernel<32, 1>), dim3(nwg), dim3(NT), 0, s, p);
   return hipGetLastError();
 }
 

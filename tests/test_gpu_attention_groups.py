@@ -1,0 +1,45 @@
+"""The attention forward with two key groups a workgroup: both sides of the
+choice (512 keys, two workgroups a CU), odd block counts, groups that see no
+key, the training statistics, and determinism, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import partir_oracle as O
+from paper_2401_11202_amd import partir as P
+from tests.gpu_common import TOL_BF16, host, say
+from tests.test_gpu_attention import make_qkv, reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,S,H,R", [
+    (1, 384, 2, 1),      # one group
+    (1, 512, 2, 1),      # two groups: the first query block has one block for each
+    (1, 640, 3, 1),
+    (2, 1152, 1, 2),     # shards of 9 blocks of 64: the second group has one less
+    (1, 1024, 2, 2),     # shards past a query block, and blocks past a wave's queries
+    (1, 1024, 64, 1),    # 512 workgroups ...
+    (1, 1024, 65, 1),    # ... and 520: one group
+])
+def test_key_groups(B, S, H, R, causal):
+    Q, K, V = make_qkv(140 + H, B, S, H)
+    rng = np.random.default_rng(140)
+    rows = np.unique(np.concatenate([[b * S + r for b in range(B) for r in (0, 63, 64, 127, 128, 191, S - 1)],
+                                     rng.choice(B * S, 40, replace=False)]))
+    say(f"attention B={B} S={S} H={H} R_kv={R} causal={causal}")
+    q, k, v = Q.to_device(), K.to_device(), V.to_device()
+    o, lse = P.attention_train(q, k, v, B=B, S=S, n_heads=H, causal=causal, R_kv=R)
+    again, lse2 = P.attention_train(q, k, v, B=B, S=S, n_heads=H, causal=causal, R_kv=R)
+    torch.cuda.synchronize()
+    assert torch.equal(o, again) and torch.equal(lse, lse2)
+    ref, nrm = reference(Q, K, V, B, S, H, causal, rows)
+    assert O.normalised_error(host(o)[rows], ref, nrm) <= TOL_BF16
+    # the log-sum-exp of the same scores by torch, one head in fp32
+    D, c = 128, 128 ** -0.5 * np.log2(np.e)
+    s = c * (q[:S, :D].float() @ k[:S, :D].float().t().contiguous())
+    if causal:
+        s.masked_fill_(torch.ones_like(s, dtype=torch.bool).triu_(1), float("-inf"))
+    want = torch.logsumexp(s * np.log(2.0), dim=1) / np.log(2.0)
+    assert float((lse[:S, 0] - want).abs().max()) < 1e-4
