@@ -20,6 +20,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -47,6 +48,27 @@ constexpr size_t kMaxPartialBytes = (size_t)64 << 20;
 
 thread_local std::string g_error;
 thread_local std::string g_plan_text;
+thread_local std::function<void()> g_deferred_text;   // builds g_plan_text of the last call, if it is wanted
+
+// Whether the plan being built on this thread needs its text: formatting takes
+// as long as planning, and only partir_last_plan_text reads what a call that
+// executes would leave.
+thread_local bool g_want_text = true;
+
+struct TextScope {
+  explicit TextScope(bool want) { g_want_text = want; }
+  ~TextScope() { g_want_text = true; }
+};
+
+// snprintf into a plan's text; empty when no text is wanted
+void textf(char* buf, size_t n, const char* fmt, ...) {
+  buf[0] = 0;
+  if (!g_want_text) return;
+  va_list ap;
+  va_start(ap, fmt);
+  vsnprintf(buf, n, fmt, ap);
+  va_end(ap);
+}
 
 int fail(int status, const char* fmt, ...) {
   char buf[512];
@@ -254,8 +276,9 @@ size_t gemm_ws_bytes(const GemmSpec& g) {
 }
 
 std::string describe_gemm(const GemmSpec& g, int64_t grid, bool split) {
+  if (!g_want_text) return std::string();
   char buf[512];
-  snprintf(buf, sizeof buf,
+  textf(buf, sizeof buf,
            "%s: C[%lld,%lld]%s = A[%lld,%lld] . B[%lld,%lld]; #tile M x%d (rows %lld/shard), "
            "#tile N x%d (cols %lld/shard)%s; #sum K x%d (%lld/shard) %s; grid %lld WGs",
            g.label, (long long)g.M, (long long)(g.N * g.ngroups), g.ngroups > 1 ? " (groups)" : "",
@@ -324,23 +347,23 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
                            split);
     char buf[200];
     if (split && g.sum_impl != PARTIR_SUM_SPLITK) {   // counted in 256 x 256 output tiles, like the tail split
-      snprintf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %lld K tiles each",
+      textf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %lld K tiles each",
                (long long)gemm_tiles(g, 256), c.parts, (long long)(c.ks / 64));
       L.text += buf;
     }
     if (c.tile != 256) {
-      snprintf(buf, sizeof buf, "; workgroup tiles of %d x %d", c.tile, c.tile);
+      textf(buf, sizeof buf, "; workgroup tiles of %d x %d", c.tile, c.tile);
       L.text += buf;
     }
     if (p.tail_parts > 1) {
-      snprintf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %d K tiles each",
+      textf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %d K tiles each",
                (long long)(ntiles - tail_base), p.tail_parts, p.tail_kt);
       L.text += buf;
       plan.launches.push_back(L);
       Launch Fx = L;
       Fx.kind = L_GEMM_BF16_FIXUP;
       Fx.name = std::string(g.name) + ".fixup";
-      snprintf(buf, sizeof buf, "%s.fixup: %lld tiles = sum of their %d K parts in ascending order, then the epilogue",
+      textf(buf, sizeof buf, "%s.fixup: %lld tiles = sum of their %d K parts in ascending order, then the epilogue",
                g.name, (long long)(ntiles - tail_base), p.tail_parts);
       Fx.text = buf;
       plan.launches.push_back(Fx);
@@ -363,8 +386,8 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     p.epi = split ? EPI_PARTIAL : EPI_F32;
     L.kind = L_GEMM_F32;
     L.name = g.name;
-    L.text = describe_gemm(g, (int64_t)p.tiles_m * p.tiles_n * p.nsplit, split) +
-             "; workgroup tiles of " + std::to_string(tile);
+    L.text = describe_gemm(g, (int64_t)p.tiles_m * p.tiles_n * p.nsplit, split);
+    if (g_want_text) L.text += "; workgroup tiles of " + std::to_string(tile);
   }
   plan.launches.push_back(L);
   if (split) {
@@ -383,11 +406,11 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     r.resid_add = g.resid_add;
     char buf[256];
     if (g.rk > 1)
-      snprintf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum_{r=0..%d} partial[r] (in-device all_reduce)%s%s",
+      textf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum_{r=0..%d} partial[r] (in-device all_reduce)%s%s",
                (long long)g.M, (long long)g.N, nparts - 1, g.bias[0] ? " + bias" : "",
                g.resid_add ? " + residual" : "");
     else
-      snprintf(buf, sizeof buf, "%s: C[%lld,%lld] = sum of the %d K parts in ascending order, then the epilogue",
+      textf(buf, sizeof buf, "%s: C[%lld,%lld] = sum of the %d K parts in ascending order, then the epilogue",
                R.name.c_str(), (long long)g.M, (long long)g.N, nparts);
     R.text = buf;
     plan.launches.push_back(R);
@@ -428,8 +451,55 @@ void keep_plan_text(const Plan& plan, const char* what) {
   for (size_t i = 0; i < plan.launches.size(); ++i)
     t += "  [" + std::to_string(i) + "] " + plan.launches[i].text + "\n";
   g_plan_text = t;
+  g_deferred_text = nullptr;
   const char* dump = getenv("PARTIR_DUMP_PLAN");
   if (dump && dump[0] == '1') fputs(t.c_str(), stderr);
+}
+
+// A pointer the plan depends on only by being there: its text is planned again
+// later with a stand-in, so that no caller's pointer outlives the call.
+template <typename T>
+void stand_in(T*& p) {
+  if (p) p = (T*)(uintptr_t)kWsAlign;
+}
+
+int check_ws(const Plan& plan, void* ws, size_t ws_bytes) {
+  if (ws_bytes < plan.ws_bytes)
+    return fail(PARTIR_E_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, plan.ws_bytes);
+  if (plan.ws_bytes > 0 && ws == nullptr) return fail(PARTIR_E_NULL, "workspace pointer is NULL");
+  if (plan.ws_bytes > 0 && !aligned16(ws)) return fail(PARTIR_E_LAYOUT, "workspace not 16-byte aligned");
+  return PARTIR_OK;
+}
+
+int execute(const Plan& plan, void* stream);
+
+// A call that executes: plans it once (with its workspace), runs it, and
+// leaves the text to partir_last_plan_text.
+template <typename Args>
+int run_plan(const char* what, const Args& a, void (*planner)(const Args&, void*, Plan&), void* ws, size_t ws_bytes,
+             void* stream) {
+  const char* dump = getenv("PARTIR_DUMP_PLAN");
+  const bool now = dump && dump[0] == '1';
+  Plan plan;
+  plan.launches.reserve(12);
+  {
+    TextScope scope(now);
+    planner(a, ws, plan);
+  }
+  const int st = check_ws(plan, ws, ws_bytes);
+  if (st) return st;
+  if (now) {
+    keep_plan_text(plan, what);
+  } else {
+    Args sizes = a;
+    sizes.drop_pointers();
+    g_deferred_text = [what, sizes, planner] {
+      Plan again;
+      planner(sizes, nullptr, again);
+      keep_plan_text(again, what);
+    };
+  }
+  return execute(plan, stream);
 }
 
 int execute(const Plan& plan, void* stream) {
@@ -461,14 +531,6 @@ int execute(const Plan& plan, void* stream) {
   return PARTIR_OK;
 }
 
-int check_ws(const Plan& plan, void* ws, size_t ws_bytes) {
-  if (ws_bytes < plan.ws_bytes)
-    return fail(PARTIR_E_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, plan.ws_bytes);
-  if (plan.ws_bytes > 0 && ws == nullptr) return fail(PARTIR_E_NULL, "workspace pointer is NULL");
-  if (plan.ws_bytes > 0 && !aligned16(ws)) return fail(PARTIR_E_LAYOUT, "workspace not 16-byte aligned");
-  return PARTIR_OK;
-}
-
 // ---------------------------------------------------------------------------
 // partir_loop_matmul
 // ---------------------------------------------------------------------------
@@ -477,6 +539,9 @@ struct MatmulArgs {
   void* C = nullptr;
   int64_t M, N, K, lda, ldb, ldc;
   int ab, c, b_layout, tile_axis, sum_axis, R, sum_impl;
+  void drop_pointers() {
+    stand_in(A); stand_in(B); stand_in(C);
+  }
 };
 
 constexpr int64_t kBf16MaxLd = (int64_t)1 << 24;
@@ -553,7 +618,7 @@ void plan_empty_sum(void* C, int64_t M, int64_t N, int64_t ldc, bool out_bf16, c
   r.C = C; r.ldc = ldc; r.bias = bias; r.resid = resid; r.ldr = ldr;
   r.act = 0; r.out_bf16 = out_bf16; r.resid_add = resid_add;
   char buf[200];
-  snprintf(buf, sizeof buf, "empty_sum: C[%lld,%lld] = sum over K = 0 (zero)%s", (long long)M, (long long)N,
+  textf(buf, sizeof buf, "empty_sum: C[%lld,%lld] = sum over K = 0 (zero)%s", (long long)M, (long long)N,
            bias ? " + bias" : "");
   R.text = buf;
   plan.launches.push_back(R);
@@ -608,6 +673,9 @@ struct MlpArgs {
   int64_t T, D, F;
   int in, out, act, Rb, Rm;
   void* Z = nullptr;   // partir_mlp_block_train: the kept pre-activation [T, F] bf16
+  void drop_pointers() {
+    stand_in(X); stand_in(W1); stand_in(b1); stand_in(W2); stand_in(b2); stand_in(Y); stand_in(Z);
+  }
 };
 
 int validate_mlp(const MlpArgs& a, bool with_ptrs) {
@@ -677,6 +745,9 @@ struct AttnArgs {
   float scale;
   int in, out, Rb, Rm;
   void* saved = nullptr;   // partir_attn_block_train: Q | K | V | O | lse kept for the backward
+  void drop_pointers() {
+    stand_in(X); stand_in(Wq); stand_in(Wk); stand_in(Wv); stand_in(Wo); stand_in(Y); stand_in(saved);
+  }
 };
 
 int validate_attn_shapes(int64_t B, int64_t S, int64_t D, int64_t H, int64_t dh, int Rb, int Rm) {
@@ -757,7 +828,7 @@ void plan_attention_launch(char* qkvo, int64_t B, int64_t S, int64_t D, int64_t 
   p.scale_log2 = sc * 1.4426950408889634f;
   p.lse = lse;
   char buf[256];
-  snprintf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads/shard) over %lld sequences x %lld heads, "
+  textf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads/shard) over %lld sequences x %lld heads, "
            "S=%lld, %s, %lld WGs", (long long)(H / Rm), (long long)B, (long long)H, (long long)S,
            causal ? "causal" : "full", (long long)(S / 128 * B * H));
   L.text = buf;
@@ -805,6 +876,10 @@ struct DecArgs {
   float eps;
   int64_t B, S, D, H, dh, F;
   int Rb, Rm;
+  void drop_pointers() {
+    stand_in(x); stand_in(g1); stand_in(g2); stand_in(Wq); stand_in(Wk); stand_in(Wv); stand_in(Wo); stand_in(W1);
+    stand_in(W2);
+  }
 };
 
 int validate_dec(const DecArgs& a, bool with_ptrs) {
@@ -831,7 +906,7 @@ void plan_rmsnorm(const float* x, const float* g, void* y, int64_t rows, int64_t
   RmsParams& p = L.rms;
   p.x = x; p.g = g; p.y = (uint16_t*)y; p.ldx = D; p.ldy = D; p.rows = (int)rows; p.D = (int)D; p.eps = eps;
   char buf[160];
-  snprintf(buf, sizeof buf, "rmsnorm: %lld rows x %lld (replicated across model shards, %d batch shards)",
+  textf(buf, sizeof buf, "rmsnorm: %lld rows x %lld (replicated across model shards, %d batch shards)",
            (long long)rows, (long long)D, Rb);
   L.text = buf;
   plan.launches.push_back(L);
@@ -905,6 +980,9 @@ struct AttnCoreArgs {
   float scale;
   int Rkv;
   float* lse = nullptr;   // partir_attention_train: per-row base-2 log-sum-exp
+  void drop_pointers() {
+    stand_in(Q); stand_in(K); stand_in(V); stand_in(O); stand_in(lse);
+  }
 };
 
 int validate_attn_core(const AttnCoreArgs& a, bool with_ptrs) {
@@ -976,8 +1054,8 @@ void plan_attn_core(const AttnCoreArgs& a, void* ws, Plan& plan) {
   p.Lpart = base ? (float*)(base + o_bytes + ml_bytes) : nullptr;
   p.lse = a.lse;
   char buf[320], part[64] = "";
-  if (parts > 1) snprintf(part, sizeof part, ", each as %d ordered parts of %d", parts, p.kb_per * 64);
-  snprintf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads) x loop s [#sum softmax](%d key shards of %d%s) "
+  if (parts > 1) textf(part, sizeof part, ", each as %d ordered parts of %d", parts, p.kb_per * 64);
+  textf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads) x loop s [#sum softmax](%d key shards of %d%s) "
            "over %lld sequences, S=%lld, %s", (long long)a.H, a.Rkv, p.kb_per * 64 * parts, part, (long long)a.B,
            (long long)a.S, a.causal ? "causal" : "full");
   L.text = buf;
@@ -986,7 +1064,7 @@ void plan_attn_core(const AttnCoreArgs& a, void* ws, Plan& plan) {
     Launch C = L;
     C.kind = L_ATTN_COMBINE;
     C.name = "attn.combine";
-    C.text = "attention_combine: O = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s, s ascending";
+    if (g_want_text) C.text = "attention_combine: O = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s, s ascending";
     plan.launches.push_back(C);
   }
 }
@@ -1001,6 +1079,10 @@ struct AttnBwdArgs {
   int64_t B = 0, S = 0, H = 0, dh = 0;
   int causal = 1;
   float scale = 0.f;
+  void drop_pointers() {
+    stand_in(Q); stand_in(K); stand_in(V); stand_in(O); stand_in(dO); stand_in(lse); stand_in(dQ); stand_in(dK);
+    stand_in(dV);
+  }
 };
 
 int validate_attn_bwd(const AttnBwdArgs& a, bool with_ptrs) {
@@ -1035,7 +1117,7 @@ void plan_attn_bwd(const AttnBwdArgs& a, void* ws, Plan& plan) {
   p.scale = a.scale > 0 ? a.scale : 1.0f / std::sqrt((float)a.dh);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   char buf[256];
-  snprintf(buf, sizeof buf, "attention_backward: loop h [#tile<1>](%lld heads) over %lld sequences, S=%lld, %s; "
+  textf(buf, sizeof buf, "attention_backward: loop h [#tile<1>](%lld heads) over %lld sequences, S=%lld, %s; "
            "dq pass (keys streamed) then dk/dv pass (queries streamed)", (long long)a.H, (long long)a.B,
            (long long)a.S, a.causal ? "causal" : "full");
   L.text = buf;
@@ -1054,6 +1136,10 @@ struct AttnBlockBwdArgs {
   int causal = 1;
   float scale = 0.f;
   int Rb = 1, Rm = 1;
+  void drop_pointers() {
+    stand_in(X); stand_in(Wq); stand_in(Wk); stand_in(Wv); stand_in(Wo); stand_in(saved); stand_in(dY); stand_in(dX);
+    stand_in(dWq); stand_in(dWk); stand_in(dWv); stand_in(dWo);
+  }
 };
 
 int validate_attn_block_bwd(const AttnBlockBwdArgs& a, bool with_ptrs) {
@@ -1133,7 +1219,7 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
       Launch& L = plan.launches[i];
       L.kind = L.kind == L_GEMM_BF16_FIXUP ? L_GEMM_BF16_PARTS_FIXUP : L_GEMM_BF16_PARTS;
       L.parts = t;
-      if (i == first) L.text += "; B^T read as K parts Wq | Wk | Wv";
+      if (g_want_text && i == first) L.text += "; B^T read as K parts Wq | Wk | Wv";
     }
   }
   const char* wnames[3] = {"bwd.dwq dWq = sum_b (slice 0 X[b])^T . dQ[b][:, m]",
@@ -1169,6 +1255,10 @@ struct MlpBwdArgs {
   void *dX = nullptr, *dW1 = nullptr, *db1 = nullptr, *dW2 = nullptr, *db2 = nullptr;
   int64_t T, D, F;
   int act, Rb, Rm;
+  void drop_pointers() {
+    stand_in(X); stand_in(W1); stand_in(b1); stand_in(W2); stand_in(dY); stand_in(Z); stand_in(dX); stand_in(dW1);
+    stand_in(db1); stand_in(dW2); stand_in(db2);
+  }
 };
 
 int validate_mlp_bwd(const MlpBwdArgs& a, bool with_ptrs) {
@@ -1203,7 +1293,7 @@ void plan_colsum(const void* in, void* partial, void* out, int64_t rows, int64_t
   L.cs.in = (const uint16_t*)in; L.cs.partial = (float*)partial; L.cs.out = (float*)out;
   L.cs.ld = cols; L.cs.rows = (int)rows; L.cs.cols = (int)cols; L.cs.partial_ready = partial_ready;
   char buf[200];
-  snprintf(buf, sizeof buf, "colsum: sum over %lld rows of [%lld,%lld], blocks of %d in order (the batch #sum of "
+  textf(buf, sizeof buf, "colsum: sum over %lld rows of [%lld,%lld], blocks of %d in order (the batch #sum of "
            "a bias gradient)%s", (long long)rows, (long long)rows, (long long)cols, kColSumChunk,
            partial_ready ? "; block sums from act_backward" : "");
   L.text = buf;
@@ -1265,7 +1355,7 @@ void plan_mlp_bwd(const MlpBwdArgs& a, void* ws, Plan& plan) {
     E.act.H = (uint16_t*)H; E.act.ld = F;
     E.act.colpart = a.db1 ? (float*)csp : nullptr;   // db1's block sums, fused
     E.act.rows = (int)T; E.act.cols = (int)F; E.act.act = a.act;
-    E.text = a.act ? "act_backward: dZ = dH * gelu'(Z); H = gelu(Z)" : "act_backward: dZ = dH; H = Z";
+    if (g_want_text) E.text = a.act ? "act_backward: dZ = dH * gelu'(Z); H = gelu(Z)" : "act_backward: dZ = dH; H = Z";
     plan.launches.push_back(E);
     g2.A = H; g2.a_mn = true; g2.B[0] = a.dY; g2.b_nk = 0; g2.C[0] = a.dW2;
     g2.lda = F; g2.ldb = D; g2.ldc = D; g2.M = F; g2.N = D; g2.K = T;
@@ -1358,7 +1448,14 @@ const char* partir_status_string(int status) {
 
 const char* partir_last_error(void) { return g_error.c_str(); }
 const char* partir_version(void) { return "libpartir 0.1 (gfx950)"; }
-const char* partir_last_plan_text(void) { return g_plan_text.c_str(); }
+const char* partir_last_plan_text(void) {
+  if (g_deferred_text) {
+    const std::function<void()> make = std::move(g_deferred_text);
+    g_deferred_text = nullptr;
+    make();
+  }
+  return g_plan_text.c_str();
+}
 
 // ---- loop_matmul ----------------------------------------------------------------
 size_t partir_loop_matmul_workspace(int64_t M, int64_t N, int64_t K, int ab_dtype, int c_dtype,
@@ -1393,11 +1490,7 @@ int partir_loop_matmul(const void* A, const void* B, void* C, int64_t M, int64_t
   MatmulArgs a{A, B, C, M, N, K, lda, ldb, ldc, ab_dtype, c_dtype, b_layout, tile_axis, sum_axis, R, sum_impl};
   int st = validate_matmul(a, true);
   if (st) return st;
-  Plan plan;
-  plan_matmul(a, ws, plan);
-  if ((st = check_ws(plan, ws, ws_bytes))) return st;
-  keep_plan_text(plan, "loop_matmul");
-  return execute(plan, stream);
+  return run_plan("loop_matmul", a, plan_matmul, ws, ws_bytes, stream);
 }
 
 // ---- mlp_block -------------------------------------------------------------------
@@ -1405,6 +1498,7 @@ size_t partir_mlp_block_workspace(int64_t T, int64_t D, int64_t F, int out_dtype
   MlpArgs a{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, T, D, F, PARTIR_BF16, out_dtype, PARTIR_ACT_GELU_ERF, R_batch, R_model};
   if (validate_mlp(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_mlp(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1427,13 +1521,7 @@ int partir_mlp_block(const void* X, const void* W1, const void* b1, const void* 
   MlpArgs a{X, W1, b1, W2, b2, Y, T, D, F, in_dtype, out_dtype, act, R_batch, R_model};
   int st = validate_mlp(a, true);
   if (st) return st;
-  Plan probe;
-  plan_mlp(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_mlp(a, ws, plan);
-  keep_plan_text(plan, "mlp_block");
-  return execute(plan, stream);
+  return run_plan("mlp_block", a, plan_mlp, ws, ws_bytes, stream);
 }
 
 int partir_mlp_block_train(const void* X, const void* W1, const void* b1, const void* W2, const void* b2,
@@ -1443,13 +1531,7 @@ int partir_mlp_block_train(const void* X, const void* W1, const void* b1, const 
   if (T * D * F > 0 && !Z) return fail(PARTIR_E_NULL, "Z must be non-NULL (unless empty)");
   int st = validate_mlp(a, true);
   if (st) return st;
-  Plan probe;
-  plan_mlp(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_mlp(a, ws, plan);
-  keep_plan_text(plan, "mlp_block_train");
-  return execute(plan, stream);
+  return run_plan("mlp_block_train", a, plan_mlp, ws, ws_bytes, stream);
 }
 
 // ---- MLP block on device-local arrays (BP + MP + Z3, activations sharded on M) ------
@@ -1464,6 +1546,11 @@ struct MlpShardedArgs {
   void* const* Y = nullptr;           // [T/(RB RM), D] per device
   int64_t T = 0, D = 0, F = 0;
   int out = PARTIR_F32, act = PARTIR_ACT_GELU_ERF, Rb = 1, Rm = 1;
+  void drop_pointers() {
+    X = W1t = W2t = nullptr;   // the part arrays are read while planning
+    Y = nullptr;
+    stand_in(b1); stand_in(b2);
+  }
 };
 
 int validate_mlp_sharded(const MlpShardedArgs& a, bool with_ptrs) {
@@ -1525,7 +1612,7 @@ void plan_mlp_sharded(const MlpShardedArgs& a, void* ws, Plan& plan) {
     Launch& L = plan.launches.back();
     L.kind = L_GEMM_BF16_PARTS;
     L.parts.reset(t);
-    L.text += how;
+    if (g_want_text) L.text += how;
   };
   GemmSpec g1;
   g1.A = nullptr; g1.B[0] = nullptr; g1.C[0] = H; g1.bias[0] = (const float*)a.b1;
@@ -1571,6 +1658,11 @@ struct DecShardedArgs {
   const void* const* W[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};   // q, k, v, o, 1, 2
   int64_t B = 0, S = 0, D = 0, H = 0, dh = 0, F = 0;
   int Rb = 1, Rm = 1;
+  void drop_pointers() {
+    x = nullptr;   // the part arrays are read while planning
+    for (auto& w : W) w = nullptr;
+    stand_in(g1); stand_in(g2);
+  }
 };
 
 int validate_dec_sharded(const DecShardedArgs& a, bool with_ptrs) {
@@ -1667,7 +1759,7 @@ void plan_dec_sharded(const DecShardedArgs& a, void* ws, Plan& plan) {
     for (int i = 0; i < nd; ++i) t->x[i] = a.x ? (const float*)a.x[i] : nullptr;
     L.rms_parts.reset(t);
     char buf[200];
-    snprintf(buf, sizeof buf, "rmsnorm: %d devices x %lld tokens x %lld, each device's own tokens (sequence-parallel), "
+    textf(buf, sizeof buf, "rmsnorm: %d devices x %lld tokens x %lld, each device's own tokens (sequence-parallel), "
              "stored into the gathered buffer (all_gather<M>)", nd, (long long)rows_dev, (long long)D);
     L.text = buf;
   };
@@ -1704,7 +1796,7 @@ void plan_dec_sharded(const DecShardedArgs& a, void* ws, Plan& plan) {
       Launch& L = plan.launches[i];
       L.kind = L.kind == L_GEMM_BF16_FIXUP ? L_GEMM_BF16_PARTS_FIXUP : L_GEMM_BF16_PARTS;
       L.parts = sp;
-      if (i == first) L.text += how;
+      if (g_want_text && i == first) L.text += how;
     }
   };
   norms(a.g1);
@@ -1728,6 +1820,7 @@ size_t partir_decoder_layer_sharded_workspace(int64_t B, int64_t S, int64_t D, i
   a.B = B; a.S = S; a.D = D; a.H = n_heads; a.dh = d_head; a.F = F; a.Rb = R_batch; a.Rm = R_model;
   if (validate_dec_sharded(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_dec_sharded(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1757,13 +1850,7 @@ int partir_decoder_layer_sharded(void* const* x_parts, const void* g1, const voi
   a.B = B; a.S = S; a.D = D; a.H = n_heads; a.dh = d_head; a.F = F; a.Rb = R_batch; a.Rm = R_model;
   int st = validate_dec_sharded(a, true);
   if (st) return st;
-  Plan probe;
-  plan_dec_sharded(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_dec_sharded(a, ws, plan);
-  keep_plan_text(plan, "decoder_layer_sharded");
-  return execute(plan, stream);
+  return run_plan("decoder_layer_sharded", a, plan_dec_sharded, ws, ws_bytes, stream);
 }
 
 size_t partir_mlp_block_sharded_workspace(int64_t T, int64_t D, int64_t F, int R_batch, int R_model) {
@@ -1771,6 +1858,7 @@ size_t partir_mlp_block_sharded_workspace(int64_t T, int64_t D, int64_t F, int R
   a.T = T; a.D = D; a.F = F; a.Rb = R_batch; a.Rm = R_model;
   if (validate_mlp_sharded(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_mlp_sharded(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1797,13 +1885,7 @@ int partir_mlp_block_sharded(const void* const* X_parts, const void* const* W1t_
   a.T = T; a.D = D; a.F = F; a.out = out_dtype; a.act = act; a.Rb = R_batch; a.Rm = R_model;
   int st = validate_mlp_sharded(a, true);
   if (st) return st;
-  Plan probe;
-  plan_mlp_sharded(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_mlp_sharded(a, ws, plan);
-  keep_plan_text(plan, "mlp_block_sharded");
-  return execute(plan, stream);
+  return run_plan("mlp_block_sharded", a, plan_mlp_sharded, ws, ws_bytes, stream);
 }
 
 // ---- attn_block ------------------------------------------------------------------
@@ -1813,6 +1895,7 @@ size_t partir_attn_block_workspace(int64_t B, int64_t S, int64_t D, int64_t n_he
              PARTIR_BF16, PARTIR_F32, R_batch, R_model};
   if (validate_attn(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_attn(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1837,13 +1920,7 @@ int partir_attn_block(const void* X, const void* Wq, const void* Wk, const void*
              in_dtype, out_dtype, R_batch, R_model};
   int st = validate_attn(a, true);
   if (st) return st;
-  Plan probe;
-  plan_attn(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn(a, ws, plan);
-  keep_plan_text(plan, "attn_block");
-  return execute(plan, stream);
+  return run_plan("attn_block", a, plan_attn, ws, ws_bytes, stream);
 }
 
 size_t partir_attn_block_saved_bytes(int64_t B, int64_t S, int64_t D, int64_t n_heads) {
@@ -1861,13 +1938,7 @@ int partir_attn_block_train(const void* X, const void* Wq, const void* Wk, const
   if (st) return st;
   if (B * S > 0 && !saved) return fail(PARTIR_E_NULL, "saved must be non-NULL");
   if (!aligned16(saved)) return fail(PARTIR_E_LAYOUT, "saved must be 16-byte aligned");
-  Plan probe;
-  plan_attn(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn(a, ws, plan);
-  keep_plan_text(plan, "attn_block_train");
-  return execute(plan, stream);
+  return run_plan("attn_block_train", a, plan_attn, ws, ws_bytes, stream);
 }
 
 size_t partir_attn_block_backward_workspace(int64_t B, int64_t S, int64_t D, int64_t n_heads, int64_t d_head,
@@ -1876,6 +1947,7 @@ size_t partir_attn_block_backward_workspace(int64_t B, int64_t S, int64_t D, int
   a.B = B; a.S = S; a.D = D; a.H = n_heads; a.dh = d_head; a.Rb = R_batch; a.Rm = R_model;
   if (validate_attn_block_bwd(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_attn_block_bwd(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1905,13 +1977,7 @@ int partir_attn_block_backward(const void* X, const void* Wq, const void* Wk, co
   a.Rb = R_batch; a.Rm = R_model;
   int st = validate_attn_block_bwd(a, true);
   if (st) return st;
-  Plan probe;
-  plan_attn_block_bwd(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn_block_bwd(a, ws, plan);
-  keep_plan_text(plan, "attn_block_backward");
-  return execute(plan, stream);
+  return run_plan("attn_block_backward", a, plan_attn_block_bwd, ws, ws_bytes, stream);
 }
 
 // ---- MLP block backward -----------------------------------------------------------
@@ -1923,6 +1989,7 @@ size_t partir_mlp_block_backward_workspace(int64_t T, int64_t D, int64_t F, int 
   if (with_bias_grads) { a.db1 = dummy; a.db2 = dummy; }
   if (validate_mlp_bwd(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_mlp_bwd(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1950,13 +2017,7 @@ int partir_mlp_block_backward(const void* X, const void* W1, const void* b1, con
   a.T = T; a.D = D; a.F = F; a.act = act; a.Rb = R_batch; a.Rm = R_model;
   int st = validate_mlp_bwd(a, true);
   if (st) return st;
-  Plan probe;
-  plan_mlp_bwd(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_mlp_bwd(a, ws, plan);
-  keep_plan_text(plan, "mlp_block_backward");
-  return execute(plan, stream);
+  return run_plan("mlp_block_backward", a, plan_mlp_bwd, ws, ws_bytes, stream);
 }
 
 // ---- attention core ---------------------------------------------------------------
@@ -1964,6 +2025,7 @@ size_t partir_attention_workspace(int64_t B, int64_t S, int64_t n_heads, int64_t
   AttnCoreArgs a{nullptr, nullptr, nullptr, nullptr, B, S, n_heads, d_head, 1, 0.f, R_kv};
   if (validate_attn_core(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_attn_core(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -1986,13 +2048,7 @@ int partir_attention(const void* Q, const void* K, const void* V, void* O, int64
   AttnCoreArgs a{Q, K, V, O, B, S, n_heads, d_head, causal ? 1 : 0, scale, R_kv};
   int st = validate_attn_core(a, true);
   if (st) return st;
-  Plan probe;
-  plan_attn_core(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn_core(a, ws, plan);
-  keep_plan_text(plan, "attention");
-  return execute(plan, stream);
+  return run_plan("attention", a, plan_attn_core, ws, ws_bytes, stream);
 }
 
 int partir_attention_train(const void* Q, const void* K, const void* V, void* O, float* lse, int64_t B, int64_t S,
@@ -2003,13 +2059,7 @@ int partir_attention_train(const void* Q, const void* K, const void* V, void* O,
   if (st) return st;
   if (B * S > 0 && !lse) return fail(PARTIR_E_NULL, "lse must be non-NULL");
   if ((uintptr_t)lse & 3) return fail(PARTIR_E_LAYOUT, "lse must be 4-byte aligned");
-  Plan probe;
-  plan_attn_core(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn_core(a, ws, plan);
-  keep_plan_text(plan, "attention_train");
-  return execute(plan, stream);
+  return run_plan("attention_train", a, plan_attn_core, ws, ws_bytes, stream);
 }
 
 size_t partir_attention_backward_workspace(int64_t B, int64_t S, int64_t n_heads, int64_t d_head) {
@@ -2017,6 +2067,7 @@ size_t partir_attention_backward_workspace(int64_t B, int64_t S, int64_t n_heads
   a.B = B; a.S = S; a.H = n_heads; a.dh = d_head;
   if (validate_attn_bwd(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_attn_bwd(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -2042,13 +2093,7 @@ int partir_attention_backward(const void* Q, const void* K, const void* V, const
   a.B = B; a.S = S; a.H = n_heads; a.dh = d_head; a.causal = causal ? 1 : 0; a.scale = scale;
   int st = validate_attn_bwd(a, true);
   if (st) return st;
-  Plan probe;
-  plan_attn_bwd(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_attn_bwd(a, ws, plan);
-  keep_plan_text(plan, "attention_backward");
-  return execute(plan, stream);
+  return run_plan("attention_backward", a, plan_attn_bwd, ws, ws_bytes, stream);
 }
 
 // ---- decoder_layer ---------------------------------------------------------------
@@ -2058,6 +2103,7 @@ size_t partir_decoder_layer_workspace(int64_t B, int64_t S, int64_t D, int64_t n
   a.eps = 1e-6f; a.B = B; a.S = S; a.D = D; a.H = n_heads; a.dh = d_head; a.F = F; a.Rb = R_batch; a.Rm = R_model;
   if (validate_dec(a, false) != PARTIR_OK) return (size_t)-1;
   Plan plan;
+  TextScope quiet(false);
   plan_dec(a, nullptr, plan);
   return plan.ws_bytes;
 }
@@ -2084,13 +2130,7 @@ int partir_decoder_layer(void* x, const void* g1, const void* g2, float eps, con
   a.eps = eps; a.B = B; a.S = S; a.D = D; a.H = n_heads; a.dh = d_head; a.F = F; a.Rb = R_batch; a.Rm = R_model;
   int st = validate_dec(a, true);
   if (st) return st;
-  Plan probe;
-  plan_dec(a, nullptr, probe);
-  if ((st = check_ws(probe, ws, ws_bytes))) return st;
-  Plan plan;
-  plan_dec(a, ws, plan);
-  keep_plan_text(plan, "decoder_layer");
-  return execute(plan, stream);
+  return run_plan("decoder_layer", a, plan_dec, ws, ws_bytes, stream);
 }
 
 // ---- trace ------------------------------------------------------------------------

@@ -63,6 +63,8 @@ class TraceEntry(ctypes.Structure):
 
 
 _lib = None
+_TILE = {None: AXIS_NONE, "M": AXIS_M, "N": AXIS_N, "K": AXIS_K}
+_SUM_IMPL = {"auto": SUM_AUTO, "fused": SUM_FUSED, "splitk": SUM_SPLITK}
 I64, I32, P, SZ, F = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
 PP = ctypes.POINTER(ctypes.c_void_p)   # a host array of device pointers
 
@@ -138,17 +140,29 @@ def _check(status: int):
         raise PartirError(status, lib().partir_last_error().decode())
 
 
+_torch = None
+
+
+def _th():
+    """torch, imported with the first call that needs it."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream(stream):
-    import torch
+    """The raw stream of a call (None: the current one)."""
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        torch = _th()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # without building a Stream object
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _dt(t) -> int:
-    import torch
+    torch = _th()
     if t.dtype == torch.bfloat16:
         return BF16
     if t.dtype == torch.float32:
@@ -157,7 +171,7 @@ def _dt(t) -> int:
 
 
 def _tdt(code: int):
-    import torch
+    torch = _th()
     return torch.bfloat16 if code == BF16 else torch.float32
 
 
@@ -172,7 +186,7 @@ def _rowmajor(t, name):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 # ---------------------------------------------------------------------------
@@ -185,14 +199,13 @@ def _bad(status: str, msg: str):
 
 def _req(t, name: str, shape, dtype, device=None):
     """A dense row-major tensor of exactly `shape` and `dtype` (on `device`)."""
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _th().Tensor):
         _bad("PARTIR_E_NULL", f"{name} must be a tensor")
     if t.dtype != dtype:
         _bad("PARTIR_E_DTYPE", f"{name} has dtype {t.dtype}, expected {dtype}")
-    if tuple(t.shape) != tuple(int(v) for v in shape):
+    if t.shape != shape and tuple(t.shape) != tuple(int(v) for v in shape):
         _bad("PARTIR_E_SHAPE", f"{name} has shape {tuple(t.shape)}, expected {tuple(int(v) for v in shape)}")
-    if t.numel() > 0 and not t.is_contiguous():
+    if not t.is_contiguous() and t.numel() > 0:
         _bad("PARTIR_E_LAYOUT", f"{name} must be contiguous (row-major)")
     if device is not None and t.device != device:
         _bad("PARTIR_E_LAYOUT", f"{name} is on {t.device}, expected {device}")
@@ -215,15 +228,18 @@ def _gpu_all(**named):
     dtypes, so that those errors are reported for CPU tensors too)."""
     dev = None
     for name, t in named.items():
-        ts = t if isinstance(t, (list, tuple)) else [t]
-        for i, u in enumerate(ts):
+        if t is None:
+            continue
+        listed = isinstance(t, (list, tuple))
+        for i, u in enumerate(t if listed else (t,)):
             if u is None:
                 continue
-            nm = name if len(ts) == 1 and not isinstance(t, (list, tuple)) else f"{name}[{i}]"
+            d = u.device
             if dev is None:
-                dev = _gpu(u, nm)
-            elif u.device != dev:
-                _bad("PARTIR_E_LAYOUT", f"{nm} is on {u.device}, expected {dev}")
+                dev = _gpu(u, f"{name}[{i}]" if listed else name)
+            elif d != dev:
+                _bad("PARTIR_E_LAYOUT", f"{name}[{i}] is on {d}, expected {dev}" if listed
+                     else f"{name} is on {d}, expected {dev}")
     return dev
 
 
@@ -231,39 +247,41 @@ def _on_stream(stream, *tensors):
     """Kernels run on `stream`: tensors allocated here on the current stream
     are marked as used there, so the caching allocator does not hand their
     memory out again before those kernels finish."""
-    import torch
+    if stream is None:
+        return
+    torch = _th()
     if isinstance(stream, torch.cuda.Stream) and stream != torch.cuda.current_stream(stream.device):
         for t in tensors:
             if t is not None and t.numel() > 0:
                 t.record_stream(stream)
 
 
-def _workspace(nbytes: int, device, ws):
-    import torch
+def _workspace(device, ws, query, *sizes):
+    """The workspace of a call and its bytes: the caller's `ws`, or a new one
+    of the size that query(*sizes) gives."""
+    if ws is not None and ws.device == device and ws.is_contiguous():
+        return ws, ws.nbytes       # the entry point compares it with what it needs
+    nbytes = query(*sizes)
     if nbytes == ctypes.c_size_t(-1).value:
         # invalid arguments: the entry point itself reports the precise status
         return None, 0
     if nbytes == 0:
         return None, 0
-    if ws is None:
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    elif ws.device != device or not ws.is_contiguous():
+    if ws is not None:
         _bad("PARTIR_E_WORKSPACE", f"workspace must be a contiguous buffer on {device}")
-    return ws, ws.numel() * ws.element_size()
+    return _th().empty(nbytes, dtype=_th().uint8, device=device), nbytes
 
 
 def _axis(name):
-    return {None: AXIS_NONE, "M": AXIS_M, "N": AXIS_N, "K": AXIS_K}[name]
+    return _TILE[name]
 
 
 def _bf16():
-    import torch
-    return torch.bfloat16
+    return _th().bfloat16
 
 
 def _f32():
-    import torch
-    return torch.float32
+    return _th().float32
 
 
 # ---------------------------------------------------------------------------
@@ -275,7 +293,7 @@ def loop_matmul(A, B, *, tile: Optional[str] = None, sum: Optional[str] = None, 
     """C = A @ B as a loop over R virtual shards.  tile in {None, 'M', 'N'},
     sum in {None, 'K'}.  b_layout 'kn': B is [K, N]; 'nk': B is given as B^T
     [N, K].  A, B and C may be row-major views with a leading dim."""
-    import torch
+    torch = _th()
     lda, ldb = _rowmajor(A, "A"), _rowmajor(B, "B")
     M, K = A.shape
     bl = B_KN if b_layout == "kn" else B_NK
@@ -288,7 +306,7 @@ def loop_matmul(A, B, *, tile: Optional[str] = None, sum: Optional[str] = None, 
     cd = ab if out_dtype is None else (BF16 if out_dtype == torch.bfloat16 else F32)
     if ab == F32:
         cd = F32 if out_dtype is None else cd
-    si = {"auto": SUM_AUTO, "fused": SUM_FUSED, "splitk": SUM_SPLITK}[sum_impl]
+    si = _SUM_IMPL[sum_impl]
     if out is not None:
         _rowmajor(out, "C")
         if tuple(out.shape) != (M, N) or out.dtype != _tdt(cd):
@@ -297,8 +315,8 @@ def loop_matmul(A, B, *, tile: Optional[str] = None, sum: Optional[str] = None, 
     fresh = out is None
     if fresh:
         out = torch.empty((M, N), dtype=_tdt(cd), device=dev)
-    nbytes = lib().partir_loop_matmul_workspace(M, N, K, ab, cd, bl, _axis(tile), _axis(sum), R, si)
-    ws, wsb = _workspace(nbytes, dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_loop_matmul_workspace, M, N, K, ab, cd, bl, _axis(tile),
+                         _axis(sum), R, si)
     _on_stream(stream, ws if workspace is None else None, out if fresh else None)
     _check(lib().partir_loop_matmul(_ptr(A), _ptr(B), _ptr(out), M, N, K, lda, ldb,
                                     _rowmajor(out, "C"), ab, cd, bl, _axis(tile), _axis(sum), R, si,
@@ -311,7 +329,7 @@ def loop_matmul_noalloc(A, B, *, tile: Optional[str] = None, sum: Optional[str] 
     """loop_matmul without a workspace: the library's per-GPU scratch array
     holds the #sum partials (see partir_loop_matmul_noalloc).  `out` must be
     given (this call allocates nothing)."""
-    import torch
+    torch = _th()
     lda, ldb = _rowmajor(A, "A"), _rowmajor(B, "B")
     M, K = A.shape
     bl = B_KN if b_layout == "kn" else B_NK
@@ -326,7 +344,7 @@ def loop_matmul_noalloc(A, B, *, tile: Optional[str] = None, sum: Optional[str] 
     if tuple(out.shape) != (M, N) or out.dtype != _tdt(cd):
         _bad("PARTIR_E_LAYOUT", f"out is {tuple(out.shape)} {out.dtype}, expected [{M}, {N}] {_tdt(cd)}")
     _gpu_all(A=A, B=B, out=out)
-    si = {"auto": SUM_AUTO, "fused": SUM_FUSED, "splitk": SUM_SPLITK}[sum_impl]
+    si = _SUM_IMPL[sum_impl]
     _check(lib().partir_loop_matmul_noalloc(_ptr(A), _ptr(B), _ptr(out), M, N, K, lda, ldb, ldc, ab, cd, bl,
                                             _axis(tile), _axis(sum), R, si, _stream(stream)))
     return out
@@ -351,15 +369,14 @@ def _mlp_shapes(X, W1, W2, b1, b2):
 
 
 def _out_dtype(out_dtype):
-    import torch
-    return F32 if out_dtype in (None, torch.float32) else BF16
+    return F32 if out_dtype in (None, _th().float32) else BF16
 
 
 def mlp_block(X, W1, W2, *, b1=None, b2=None, R_batch: int = 1, R_model: int = 1, act: str = "gelu",
               out_dtype=None, out=None, workspace=None, stream=None):
     """Y = loop b[#tile<0>](R_batch){ loop m[#sum](R_model){ act(X_b W1[:, m] + b1_m) W2[m, :] } + b2 }.
     X [T, D], W1 [D, F], W2 [F, D] bf16 ([fan_in, fan_out]); b1 [F], b2 [D] fp32."""
-    import torch
+    torch = _th()
     T, D, F = _mlp_shapes(X, W1, W2, b1, b2)
     od = _out_dtype(out_dtype)
     _opt(out, "out", (T, D), _tdt(od))
@@ -367,7 +384,7 @@ def mlp_block(X, W1, W2, *, b1=None, b2=None, R_batch: int = 1, R_model: int = 1
     fresh = out is None
     if fresh:
         out = torch.empty((T, D), dtype=_tdt(od), device=dev)
-    ws, wsb = _workspace(mlp_block_workspace(T, D, F, od, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, mlp_block_workspace, T, D, F, od, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, out if fresh else None)
     _check(lib().partir_mlp_block(_ptr(X), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), _ptr(out), T, D, F,
                                   BF16, od, ACT_GELU if act == "gelu" else ACT_NONE, R_batch, R_model,
@@ -379,7 +396,7 @@ def mlp_block_train(X, W1, W2, *, b1=None, b2=None, R_batch: int = 1, R_model: i
                     out_dtype=None, out=None, Z=None, workspace=None, stream=None):
     """mlp_block that also keeps the pre-activation Z = X W1 + b1 [T, F] bf16
     for mlp_block_backward.  Returns (Y, Z)."""
-    import torch
+    torch = _th()
     T, D, F = _mlp_shapes(X, W1, W2, b1, b2)
     od = _out_dtype(out_dtype)
     _opt(out, "out", (T, D), _tdt(od))
@@ -390,7 +407,7 @@ def mlp_block_train(X, W1, W2, *, b1=None, b2=None, R_batch: int = 1, R_model: i
         out = torch.empty((T, D), dtype=_tdt(od), device=dev)
     if fresh_z:
         Z = torch.empty((T, F), dtype=torch.bfloat16, device=dev)
-    ws, wsb = _workspace(mlp_block_workspace(T, D, F, od, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, mlp_block_workspace, T, D, F, od, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, out if fresh_y else None, Z if fresh_z else None)
     _check(lib().partir_mlp_block_train(_ptr(X), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), _ptr(out), _ptr(Z),
                                         T, D, F, BF16, od, ACT_GELU if act == "gelu" else ACT_NONE, R_batch,
@@ -405,7 +422,7 @@ def mlp_block_backward(X, W1, W2, dY, *, b1=None, Z=None, R_batch: int = 1, R_mo
     with bias_grads, db1 [F] and db2 [D].  ``Z``: the pre-activation kept by
     mlp_block_train (else recomputed); ``out``: a tuple of the result tensors
     to write into."""
-    import torch
+    torch = _th()
     T, D, F = _mlp_shapes(X, W1, W2, b1, None)
     _req(dY, "dY", (T, D), _bf16())
     _opt(Z, "Z", (T, F), _bf16())
@@ -422,8 +439,8 @@ def mlp_block_backward(X, W1, W2, dY, *, b1=None, Z=None, R_batch: int = 1, R_mo
         out = tuple(torch.empty(sh, dtype=torch.float32, device=dev) for sh in shapes)
     dX, dW1, dW2 = out[:3]
     db1, db2 = out[3:5] if bias_grads else (None, None)
-    nbytes = lib().partir_mlp_block_backward_workspace(T, D, F, a, int(bias_grads), R_batch, R_model)
-    ws, wsb = _workspace(nbytes, dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_mlp_block_backward_workspace, T, D, F, a, int(bias_grads),
+                         R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, *(out if fresh else ()))
     _check(lib().partir_mlp_block_backward(_ptr(X), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(dY), _ptr(Z), _ptr(dX),
                                            _ptr(dW1), _ptr(db1), _ptr(dW2), _ptr(db2), T, D, F, a, R_batch,
@@ -456,7 +473,7 @@ def mlp_block_sharded(X_parts, W1t_parts, W2t_parts, *, R_batch: int, R_model: i
     D/R_batch cols b]; W2t_parts[p] = W2^T[D/R_batch rows b, F/R_model cols m]
     (the transposed blocks: device-local arrays are read K-contiguous).
     Returns the list of Y parts (token rows p of Y)."""
-    import torch
+    torch = _th()
     nd = R_batch * R_model
     if not X_parts or not W1t_parts or len(X_parts) != nd or len(W1t_parts) != nd:
         _bad("PARTIR_E_SHAPE", f"{nd} X and W1t parts expected")
@@ -476,7 +493,7 @@ def mlp_block_sharded(X_parts, W1t_parts, W2t_parts, *, R_batch: int, R_model: i
     fresh = out_parts is None
     if fresh:
         out_parts = [torch.empty((rows, D), dtype=_tdt(od), device=dev) for _ in range(nd)]
-    ws, wsb = _workspace(lib().partir_mlp_block_sharded_workspace(T, D, F, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_mlp_block_sharded_workspace, T, D, F, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, *(out_parts if fresh else ()))
     xs, w1s, w2s, ys = (_ptr_array(v) for v in (X_parts, W1t_parts, W2t_parts, out_parts))
     _check(lib().partir_mlp_block_sharded(xs, w1s, _ptr(b1), w2s, _ptr(b2), ys, T, D, F, od,
@@ -544,8 +561,8 @@ def decoder_layer_sharded(x_parts, g1, g2, W_parts, *, B: int, S: int, n_heads: 
     _parts(W_parts["W1"], "W1", nd, (F // R_model, D // R_batch), bf)
     _parts(W_parts["W2"], "W2", nd, (D // R_batch, F // R_model), bf)
     dev = _gpu_all(x_parts=x_parts, g1=g1, g2=g2, **{k: W_parts[k] for k in ("Wq", "Wk", "Wv", "Wo", "W1", "W2")})
-    nbytes = lib().partir_decoder_layer_sharded_workspace(B, S, D, n_heads, d_head, F, R_batch, R_model)
-    ws, wsb = _workspace(nbytes, dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_decoder_layer_sharded_workspace, B, S, D, n_heads, d_head, F,
+                         R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None)
     ws_ = [_ptr_array(W_parts[k]) for k in ("Wq", "Wk", "Wv", "Wo", "W1", "W2")]
     _check(lib().partir_decoder_layer_sharded(_ptr_array(x_parts), _ptr(g1), _ptr(g2), eps, *ws_, B, S, D, n_heads,
@@ -587,7 +604,7 @@ def attn_block(X, Wq, Wk, Wv, Wo, *, B: int, S: int, n_heads: int, d_head: int =
                out_dtype=None, out=None, workspace=None, stream=None):
     """Y = loop b [#tile<0>] loop m [#sum] (heads #tile attention) . Wo[m]:
     X [B*S, D] bf16; Wq, Wk, Wv, Wo [D, D] bf16 ([fan_in, fan_out])."""
-    import torch
+    torch = _th()
     T, D = _attn_shapes(X, (Wq, Wk, Wv, Wo), B, S)
     od = _out_dtype(out_dtype)
     _opt(out, "out", (T, D), _tdt(od))
@@ -595,7 +612,7 @@ def attn_block(X, Wq, Wk, Wv, Wo, *, B: int, S: int, n_heads: int, d_head: int =
     fresh = out is None
     if fresh:
         out = torch.empty((T, D), dtype=_tdt(od), device=dev)
-    ws, wsb = _workspace(attn_block_workspace(B, S, D, n_heads, d_head, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, attn_block_workspace, B, S, D, n_heads, d_head, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, out if fresh else None)
     _check(lib().partir_attn_block(_ptr(X), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(out),
                                    B, S, D, n_heads, d_head, int(causal), float(scale), BF16, od,
@@ -614,15 +631,14 @@ def attention(Q, K, V, *, B: int, S: int, n_heads: int, d_head: int = 128, causa
               scale: float = 0.0, R_kv: int = 1, out=None, workspace=None, stream=None):
     """O = softmax attention per (sequence, head), the key axis a loop of R_kv
     shards reduced with the (max, sum, output) combiner.  Q, K, V, O: [B*S, n_heads*d_head] bf16."""
-    import torch
+    torch = _th()
     T, D = _qkv_shapes((Q, K, V), ("Q", "K", "V"), B, S, n_heads, d_head)
     _opt(out, "out", (T, D), _bf16())
     dev = _gpu_all(Q=Q, K=K, V=V, out=out)
     fresh = out is None
     if fresh:
         out = torch.empty((T, D), dtype=torch.bfloat16, device=dev)
-    nbytes = lib().partir_attention_workspace(B, S, n_heads, d_head, R_kv)
-    ws, wsb = _workspace(nbytes, dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_attention_workspace, B, S, n_heads, d_head, R_kv)
     _on_stream(stream, ws if workspace is None else None, out if fresh else None)
     _check(lib().partir_attention(_ptr(Q), _ptr(K), _ptr(V), _ptr(out), B, S, n_heads, d_head, int(causal),
                                   float(scale), R_kv, _ptr(ws), wsb, _stream(stream)))
@@ -633,7 +649,7 @@ def attention_train(Q, K, V, *, B: int, S: int, n_heads: int, d_head: int = 128,
                     scale: float = 0.0, R_kv: int = 1, out=None, lse=None, workspace=None, stream=None):
     """attention that also returns the per-row base-2 log-sum-exp [B*S, n_heads]
     fp32 for attention_backward.  Returns (O, lse)."""
-    import torch
+    torch = _th()
     T, D = _qkv_shapes((Q, K, V), ("Q", "K", "V"), B, S, n_heads, d_head)
     _opt(out, "out", (T, D), _bf16())
     _opt(lse, "lse", (T, n_heads), _f32())
@@ -643,7 +659,7 @@ def attention_train(Q, K, V, *, B: int, S: int, n_heads: int, d_head: int = 128,
         out = torch.empty((T, D), dtype=torch.bfloat16, device=dev)
     if fresh_l:
         lse = torch.empty((T, n_heads), dtype=torch.float32, device=dev)
-    ws, wsb = _workspace(lib().partir_attention_workspace(B, S, n_heads, d_head, R_kv), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_attention_workspace, B, S, n_heads, d_head, R_kv)
     _on_stream(stream, ws if workspace is None else None, out if fresh_o else None, lse if fresh_l else None)
     _check(lib().partir_attention_train(_ptr(Q), _ptr(K), _ptr(V), _ptr(out), _ptr(lse), B, S, n_heads, d_head,
                                         int(causal), scale, R_kv, _ptr(ws), wsb, _stream(stream)))
@@ -654,7 +670,7 @@ def attention_backward(Q, K, V, O, dO, lse, *, B: int, S: int, n_heads: int, d_h
                        causal: bool = True, scale: float = 0.0, out=None, workspace=None, stream=None):
     """Gradients (dQ, dK, dV) of attention for the output cotangent dO (bf16,
     the layout of Q, K, V), from the forward's O and lse."""
-    import torch
+    torch = _th()
     T, D = _qkv_shapes((Q, K, V, O, dO), ("Q", "K", "V", "O", "dO"), B, S, n_heads, d_head)
     _req(lse, "lse", (T, n_heads), _f32())
     if out is not None:
@@ -665,7 +681,7 @@ def attention_backward(Q, K, V, O, dO, lse, *, B: int, S: int, n_heads: int, d_h
     fresh = out is None
     if fresh:
         out = tuple(torch.empty((T, D), dtype=torch.bfloat16, device=dev) for _ in range(3))
-    ws, wsb = _workspace(lib().partir_attention_backward_workspace(B, S, n_heads, d_head), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_attention_backward_workspace, B, S, n_heads, d_head)
     _on_stream(stream, ws if workspace is None else None, *(out if fresh else ()))
     _check(lib().partir_attention_backward(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(lse), _ptr(out[0]),
                                            _ptr(out[1]), _ptr(out[2]), B, S, n_heads, d_head, int(causal), scale,
@@ -678,7 +694,7 @@ def attn_block_train(X, Wq, Wk, Wv, Wo, *, B: int, S: int, n_heads: int, d_head:
                      saved=None, workspace=None, stream=None):
     """attn_block that also keeps Q, K, V, A and lse in `saved` (a uint8
     tensor) for attn_block_backward.  Returns (Y, saved)."""
-    import torch
+    torch = _th()
     T, D = _attn_shapes(X, (Wq, Wk, Wv, Wo), B, S)
     need = lib().partir_attn_block_saved_bytes(B, S, D, n_heads)
     if out is not None:
@@ -693,7 +709,7 @@ def attn_block_train(X, Wq, Wk, Wv, Wo, *, B: int, S: int, n_heads: int, d_head:
         out = torch.empty((T, D), dtype=torch.float32, device=dev)
     if fresh_s:
         saved = torch.empty(max(1, need), dtype=torch.uint8, device=dev)
-    ws, wsb = _workspace(attn_block_workspace(B, S, D, n_heads, d_head, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, attn_block_workspace, B, S, D, n_heads, d_head, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None, out if fresh_y else None, saved if fresh_s else None)
     _check(lib().partir_attn_block_train(_ptr(X), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(out),
                                          _ptr(saved), B, S, D, n_heads, d_head, int(causal), scale, BF16,
@@ -705,7 +721,7 @@ def attn_block_backward(X, Wq, Wk, Wv, Wo, saved, dY, *, B: int, S: int, n_heads
                         d_head: int = 128, causal: bool = True, scale: float = 0.0, R_batch: int = 1,
                         R_model: int = 1, out=None, workspace=None, stream=None):
     """Gradients (dX, dWq, dWk, dWv, dWo), fp32, the weights' [fan_in, fan_out] layout."""
-    import torch
+    torch = _th()
     T, D = _attn_shapes(X, (Wq, Wk, Wv, Wo), B, S)
     need = lib().partir_attn_block_saved_bytes(B, S, D, n_heads)
     if saved.dtype != torch.uint8 or saved.numel() < need:
@@ -721,8 +737,8 @@ def attn_block_backward(X, Wq, Wk, Wv, Wo, saved, dY, *, B: int, S: int, n_heads
     fresh = out is None
     if fresh:
         out = tuple(torch.empty(sh, dtype=torch.float32, device=dev) for sh in shapes)
-    ws, wsb = _workspace(lib().partir_attn_block_backward_workspace(B, S, D, n_heads, d_head, R_batch, R_model),
-                         dev, workspace)
+    ws, wsb = _workspace(dev, workspace, lib().partir_attn_block_backward_workspace, B, S, D, n_heads, d_head, R_batch,
+                         R_model)
     _on_stream(stream, ws if workspace is None else None, *(out if fresh else ()))
     _check(lib().partir_attn_block_backward(_ptr(X), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(saved),
                                             _ptr(dY), *(_ptr(o) for o in out), B, S, D, n_heads, d_head,
@@ -766,7 +782,7 @@ def decoder_layer(x, g1, g2, Wq, Wk, Wv, Wo, W1, W2, *, B: int, S: int, n_heads:
     _req(W1, "W1", (D, F), bf)
     _req(W2, "W2", (F, D), bf)
     dev = _gpu_all(x=x, g1=g1, g2=g2, Wq=Wq, Wk=Wk, Wv=Wv, Wo=Wo, W1=W1, W2=W2)
-    ws, wsb = _workspace(decoder_layer_workspace(B, S, D, n_heads, d_head, F, R_batch, R_model), dev, workspace)
+    ws, wsb = _workspace(dev, workspace, decoder_layer_workspace, B, S, D, n_heads, d_head, F, R_batch, R_model)
     _on_stream(stream, ws if workspace is None else None)
     _check(lib().partir_decoder_layer(_ptr(x), _ptr(g1), _ptr(g2), float(eps), _ptr(Wq), _ptr(Wk), _ptr(Wv),
                                       _ptr(Wo), _ptr(W1), _ptr(W2), B, S, D, n_heads, d_head, F,
