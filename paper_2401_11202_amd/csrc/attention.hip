@@ -50,14 +50,21 @@ __device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { re
 // KG = 2: eight waves in two groups that share the queries and split the keys,
 // group kg taking every other block of BKV = 64 through LDS stages of its own
 // (128 KiB in all); at the end the first group folds the second's (m, l, O) into
-// its own, the combiner of the key shards.  A grid of up to two workgroups a
-// CU is bound by its longest workgroups, whose waves are one chain of S^T,
-// exponentials and P V per block: two chains a SIMD overlap, and each is half
-// as long.  Measured (1 / 2 groups, launch): 8192 keys x 2 heads 147 / 108 us,
-// 4096 x 8 heads 87 / 62, 2048 x 20 heads 51 / 39, 1024 x 32 (sequence, head)s
-// 29 / 25.  Not below 512 keys (256 keys 12.8 / 13.4: the merge costs more) nor on
-// larger grids, where 32-key blocks at three workgroups a CU do better (3 x 2048
-// x 16: 81 either way).  More stages (loads three blocks ahead) changed nothing.
+// its own, the combiner of the key shards.  A short grid is bound by its
+// longest workgroups, whose waves are one chain of S^T, exponentials and P V
+// per block: two chains a SIMD overlap, and each is half as long.  Measured
+// (1 / 2 groups, us of a pass): unsplit causal 8192 keys x 2 heads 157 / 103,
+// 4096 x 8 heads 82 / 59, 1024 x 32 heads 26 / 22, full 4096 x 8 heads 83 / 70.
+// The 128 KiB hold a CU to one workgroup, so the line lies at one a CU: with a
+// second round, full masks lose (4096 x 10 heads 100 / 124, 2048 x 32 heads 70
+// / 77) and so do short shards (2 x 1024 keys, 16 heads 41 / 51).  Under a
+// causal mask the rounds even out where workgroups differ much in length, the
+// light ones filling in: unsplit from 2048 keys to two a CU (4096 x 12 heads 87 /
+// 65, 2048 x 32 52 / 47; 3072 x 24, 576 workgroups, 81 / 88), key shards of 1536
+// and more to one and a half (2 x 2048 keys, 5 heads 55 / 42, 2 x 4096, 3 heads
+// 98 / 75; 4 x 2048, 2 heads, 512 workgroups 60 / 74).  Not below 512 keys (256
+// a shard, 5 heads 15.4 / 15.9: the merge costs more).  More stages (loads three
+// blocks ahead) changed nothing.
 template <int BKV, int KG>
 __global__ __launch_bounds__(NT * KG, KG == 1 && BKV == 32 ? 3 : 2)
 void attention_kernel(AttnParams p) {
@@ -400,7 +407,10 @@ hipError_t launch_attention(const AttnParams& p, hipStream_t s) {
   }
   // the bounds are those of the kernel's comment
   const int keys = p.nsplit > 1 ? p.kb_per * 64 : p.S;
-  if (keys >= 512 && nwg <= 2 * (unsigned)ncu)
+  unsigned two_groups = keys >= 512 ? (unsigned)ncu : 0;
+  if (p.causal && p.nsplit == 1 && keys >= 2048) two_groups = 2 * (unsigned)ncu;
+  if (p.causal && p.nsplit > 1 && keys >= 1536) two_groups = (unsigned)ncu + (unsigned)ncu / 2;
+  if (nwg <= two_groups)
     hipLaunchKernelGGL((attention_kernel<64, 2>), dim3(nwg), dim3(2 * NT), 0, s, p);
   else if (nwg < (unsigned)ncu)
     hipLaunchKernelGGL((attention_kernel<64, 1>), dim3(nwg), dim3(NT), 0, s, p);

@@ -1,5 +1,5 @@
 """The attention forward with two key groups a workgroup: both sides of the
-choice (512 keys, two workgroups a CU), odd block counts, groups that see no
+choice (512 keys; one workgroup a CU, two or one and a half under a causal mask), odd block counts, groups that see no
 key, the training statistics, and determinism, against the oracle."""
 import numpy as np
 import pytest
@@ -20,8 +20,13 @@ pytestmark = pytest.mark.gpu
     (1, 640, 3, 1),
     (2, 1152, 1, 2),     # shards of 9 blocks of 64: the second group has one less
     (1, 1024, 2, 2),     # shards past a query block, and blocks past a wave's queries
-    (1, 1024, 64, 1),    # 512 workgroups ...
-    (1, 1024, 65, 1),    # ... and 520: one group
+    (1, 1024, 32, 1),    # 256 workgroups ...
+    (1, 1024, 33, 1),    # ... and 264: one group
+    (1, 1024, 64, 1),
+    (1, 1024, 65, 1),
+    (1, 2048, 32, 1),    # 512 workgroups: two groups under a causal mask only ...
+    (1, 2048, 33, 1),    # ... and 528: one group
+    (1, 3072, 8, 2),     # 384 workgroups over shards of 1536: two groups under a causal mask only
 ])
 def test_key_groups(B, S, H, R, causal):
     Q, K, V = make_qkv(140 + H, B, S, H)
