@@ -1011,14 +1011,23 @@ int validate_attn_core(const AttnCoreArgs& a, bool with_ptrs) {
 // key order by the combine like the shards themselves: the same #sum, in
 // smaller pieces.  The combine reads, for each row, only the parts whose
 // first key is at or before it.
+// Every part writes and the combine reads an fp32 output row, which parts of
+// less than 64 blocks repay only while the grid has fewer than the three
+// workgroups a CU that the 32-key kernel holds: 2 shards of 4096 keys, 5 heads (640
+// workgroups) 119 us in 1 part, 109 in 2, 125 in 4; 2 of 2048, 20 heads (1280) 115 /
+// 140; 4 of 2048, 3 heads (768) 84 / 85; 4 of 2048, 2 heads (512) 64 / 58.
 int attn_core_parts(int64_t B, int64_t S, int64_t H, int causal, int Rkv) {
   constexpr int64_t kFillWorkgroups = 4 * 256 * 2;
   constexpr int64_t kMinPartBlocks = 16;
+  constexpr int64_t kShortGrid = 3 * 256, kLongPartBlocks = 64;
   if (!causal || Rkv < 2) return 1;
   const int64_t kbs = S / 64 / Rkv, wgs = (S / 128) * B * H * Rkv;
   int parts = 1;
-  while (parts < 4 && wgs * parts < kFillWorkgroups && kbs % (2 * parts) == 0 && kbs / (2 * parts) >= kMinPartBlocks)
+  while (parts < 4 && kbs % (2 * parts) == 0) {
+    const bool long_parts = kbs / (2 * parts) >= kLongPartBlocks;
+    if (kbs / (2 * parts) < kMinPartBlocks || wgs * parts >= (long_parts ? kFillWorkgroups : kShortGrid)) break;
     parts *= 2;
+  }
   return parts;
 }
 
