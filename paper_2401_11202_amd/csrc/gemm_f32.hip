@@ -16,7 +16,7 @@
 // Bound by the matrix cores (157 TFLOP/s): 64 cycles per MFMA against 16 bytes
 // of LDS reads per lane and four MFMAs.  Against one 32x32 accumulator a wave
 // over a single register-staged LDS buffer (the long-rows kernel below, which
-// used to run every size): 1800 x 2056 x 2048 204 -> 134 us (74 -> 113 TFLOP/s),
+// used to run every size): 1800 x 2056 x 2048 204 -> 126 us (74 -> 120 TFLOP/s),
 // 4096^3 at 144 TFLOP/s.
 #include "kernels.h"
 #include "lds_dma.h"
