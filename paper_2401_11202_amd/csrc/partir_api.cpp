@@ -719,7 +719,11 @@ void plan_mlp(const MlpArgs& a, void* ws, Plan& plan) {
   g2.name = "mlp.down";
   g2.label = "mlp.down Y = sum_m H[:, m] . slice 0 W2[m]";
   void* part = ws ? base + h_bytes : nullptr;   // split-K / tail parts, one GEMM at a time
-  plan.ws_bytes = h_bytes + std::max(gemm_ws_bytes(g1), gemm_ws_bytes(g2));
+  // One size for the calls with and without a kept Z, which rules out the
+  // up-projection's K parts and so leads to another plan of it.
+  GemmSpec other = g1;
+  other.split_ok = !g1.split_ok;
+  plan.ws_bytes = h_bytes + std::max({gemm_ws_bytes(g1), gemm_ws_bytes(other), gemm_ws_bytes(g2)});
   plan.n_shards = a.Rb * a.Rm;
   plan.n_tile_loops = (a.Rb > 1) + 1;
   plan.flops = 4.0 * a.T * a.D * a.F;
