@@ -174,6 +174,10 @@ bool gemm_uses_splitk(const GemmSpec& g) {
   return g.rm * cdiv(g.M / g.rm, tile) * g.ngroups * g.rn * cdiv(g.N / g.rn, tile) < kNumCU;
 }
 
+// A caller's PARTIR_SUM_FUSED: every output is one accumulator over all K, so
+// neither K parts nor a split last wave.
+bool gemm_one_accumulator(const GemmSpec& g) { return g.rk > 1 && g.sum_impl == PARTIR_SUM_FUSED; }
+
 // Load balance of the last wave of 256-wide tiles: with ntiles = q * kNumCU + r output tiles
 // (0 < r <= kNumCU / 2), the r tiles of the partial last wave run as `parts`
 // workgroups each over consecutive K ranges, so the last wave holds
@@ -182,7 +186,7 @@ bool gemm_uses_splitk(const GemmSpec& g) {
 // epilogue.  Returns parts (1: no split) and the first split tile.
 int gemm_tail_parts(const GemmSpec& g, int64_t* tail_base) {
   *tail_base = 0;
-  if (!g.tail_ok || g.ab_dtype != PARTIR_BF16) return 1;
+  if (!g.tail_ok || g.ab_dtype != PARTIR_BF16 || gemm_one_accumulator(g)) return 1;
   const int64_t ntiles = gemm_tiles(g, gemm_bf16_tile_m()), r = ntiles % kNumCU, nk = cdiv(g.K, 64);
   if (g.split_ok && ntiles < kNumCU) return 1;   // less than one wave: gemm_tiling splits every tile instead
   int parts = 1;
@@ -231,7 +235,7 @@ GemmTiling gemm_tiling(const GemmSpec& g) {
   const int64_t nk = cdiv(g.K, 64);
   const bool shard_parts = g.rk > 1 && g.sum_impl == PARTIR_SUM_SPLITK;   // one partial per #sum shard
   // a product without a #sum whose output is one 256-wide tile needs no workspace
-  const bool may_split = g.split_ok && (g.rk > 1 || gemm_tiles(g, 256) > 1);
+  const bool may_split = g.split_ok && !gemm_one_accumulator(g) && (g.rk > 1 || gemm_tiles(g, 256) > 1);
   double best_us = 0;
   for (int tile = 256; tile >= 64; tile /= 2) {
     for (int want = 1; want <= 4; want *= 2) {
@@ -1244,7 +1248,7 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
     gw.A = a.X; gw.a_mn = true;
     gw.B[0] = dQKV ? (char*)dQKV + i * D * 2 : nullptr; gw.b_nk = 0; gw.C[0] = dW[i];
     gw.lda = D; gw.ldb = 3 * D; gw.ldc = D; gw.M = D; gw.N = D; gw.K = T;
-    gw.c_dtype = PARTIR_F32; gw.rn = a.Rm; gw.rk = a.Rb; gw.sum_impl = PARTIR_SUM_FUSED;
+    gw.c_dtype = PARTIR_F32; gw.rn = a.Rm; gw.rk = a.Rb;
     gw.tail_ok = gw.split_ok = true;
     gw.name = "attn.bwd.dwqkv"; gw.label = wnames[i];
     plan_gemm(gw, part, plan);
@@ -1648,7 +1652,7 @@ void plan_mlp_sharded(const MlpShardedArgs& a, void* ws, Plan& plan) {
   g2.A = H; g2.B[0] = nullptr; g2.C[0] = nullptr; g2.bias[0] = (const float*)a.b2;
   g2.lda = F; g2.ldb = F / a.Rm; g2.ldc = D;
   g2.M = T; g2.N = D; g2.K = F;
-  g2.c_dtype = a.out; g2.rm = a.Rb; g2.rk = a.Rm; g2.sum_impl = PARTIR_SUM_FUSED;
+  g2.c_dtype = a.out; g2.rm = a.Rb; g2.rk = a.Rm;
   g2.name = "mlp.down";
   g2.label = "mlp.down Y = reduce_scatter<M>(sum_m H[:, m] . all_gather<B>(W2)[m, :])";
   GemmParts* t2 = new GemmParts{};
@@ -1746,7 +1750,7 @@ void plan_dec_sharded(const DecShardedArgs& a, void* ws, Plan& plan) {
   GemmSpec go;
   go.A = qkvo ? qkvo + 3 * one : nullptr; go.resid_add = true;
   go.lda = D; go.ldb = D / a.Rm; go.ldc = D; go.M = T; go.N = D; go.K = D;
-  go.c_dtype = PARTIR_F32; go.rm = a.Rb; go.rk = a.Rm; go.sum_impl = PARTIR_SUM_FUSED; go.tail_ok = true;
+  go.c_dtype = PARTIR_F32; go.rm = a.Rb; go.rk = a.Rm; go.tail_ok = true;
   go.name = "attn.out"; go.label = "dec.attn_out x_bm += reduce_scatter<M>(sum_m O[:, m] . all_gather<B>(Wo)[m])";
   GemmSpec g1;
   g1.A = xn; g1.C[0] = Hf;
@@ -1756,7 +1760,7 @@ void plan_dec_sharded(const DecShardedArgs& a, void* ws, Plan& plan) {
   GemmSpec g2;
   g2.A = Hf; g2.resid_add = true;
   g2.lda = F; g2.ldb = F / a.Rm; g2.ldc = D; g2.M = T; g2.N = D; g2.K = F;
-  g2.c_dtype = PARTIR_F32; g2.rm = a.Rb; g2.rk = a.Rm; g2.sum_impl = PARTIR_SUM_FUSED; g2.tail_ok = true;
+  g2.c_dtype = PARTIR_F32; g2.rm = a.Rb; g2.rk = a.Rm; g2.tail_ok = true;
   g2.name = "mlp.down"; g2.label = "dec.ffn_down x_bm += reduce_scatter<M>(sum_m H[:, m] . all_gather<B>(W2)[m])";
   plan.ws_bytes = xn_bytes + core + std::max(gemm_ws_bytes(gq), gemm_ws_bytes(go));
   if (F > 0) plan.ws_bytes = xn_bytes + core + h_bytes +

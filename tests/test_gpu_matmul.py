@@ -228,12 +228,12 @@ def test_degenerate_shard_sizes(dtype):
 def test_bf16_last_wave_split_ragged(tile, summ, R, out):
     M, N, K = 1000, 304, 4112
     plan = P.plan_loop_matmul(M, N, K, ab=P.BF16, c=P.F32 if out == torch.float32 else P.BF16,
-                              tile=tile, sum=summ, R=R, sum_impl=P.SUM_FUSED)
+                              tile=tile, sum=summ, R=R, sum_impl=P.SUM_AUTO)
     assert "K parts of 17 K tiles" in plan["text"], plan["text"]
     A = I.gaussian(121, 0, (M, K), 1.0, "bf16")
     B = I.gaussian(121, 1, (K, N), K ** -0.5, "bf16")
     say(f"bf16 last-wave split {M}x{N}x{K} tile={tile} sum={summ} R={R} out={out}")
-    C = run(A, B, tile, summ, R, "nk", out_dtype=out, sum_impl="fused")
+    C = run(A, B, tile, summ, R, "nk", out_dtype=out)
     err = check(A, B, C, tile, summ, R, TOL_BF16)
     assert err <= accum_bound(K) + (2.0 ** -8 if out == torch.bfloat16 else 0.0)
 

@@ -91,3 +91,26 @@ def test_k_parts_equal_their_ordered_sum():
     assert "K parts" in P.plan_loop_matmul(M, N, K)["text"]
     for layout in ("kn", "nk"):
         assert np.array_equal(host(product(A, B, layout)), O.matmul(A.f64(), B.f64()))
+
+
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("rows,R", [(304, 3), (200, 9), (1000, 3)])
+def test_a_fused_sum_is_one_accumulator(rows, R, layout):
+    """Short grids, where the planner would cut K: a fused #sum has the bits of
+    the unsplit 256-wide tiles."""
+    M, N, K = 8192, 2048, 4104
+    A = I.gaussian(205, 0, (M, K), 1.0, "bf16")
+    B = I.gaussian(205, 1, (K, N), K ** -0.5, "bf16")
+    lay = P.B_KN if layout == "kn" else P.B_NK
+    whole_text = P.plan_loop_matmul(M, N, K, b_layout=lay)["text"]
+    assert "workgroup tiles" not in whole_text and "K parts" not in whole_text
+    plan = P.plan_loop_matmul(rows, 512, K, b_layout=lay, sum="K", R=R, sum_impl=P.SUM_FUSED)
+    assert plan["n_launches"] == 1 and plan["n_sum_splitk"] == 0
+    Ad = A.to_device()
+    Bd = (B if layout == "kn" else I.transposed(B)).to_device()
+    few = Bd[:, :512] if layout == "kn" else Bd[:512]
+    say(f"bf16 fused #sum {rows}x512x{K} R={R} {layout}")
+    whole = P.loop_matmul(Ad, Bd, b_layout=layout, out_dtype=torch.float32)
+    part = P.loop_matmul(Ad[:rows], few, sum="K", R=R, sum_impl="fused", b_layout=layout, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert torch.equal(part, whole[:rows, :512])
