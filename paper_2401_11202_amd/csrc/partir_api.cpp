@@ -174,6 +174,9 @@ bool gemm_uses_splitk(const GemmSpec& g) {
   return g.rm * cdiv(g.M / g.rm, tile) * g.ngroups * g.rn * cdiv(g.N / g.rn, tile) < kNumCU;
 }
 
+// PARTIR_SUM_SPLITK: one partial per #sum shard.
+bool gemm_shard_parts(const GemmSpec& g) { return g.rk > 1 && g.sum_impl == PARTIR_SUM_SPLITK; }
+
 // A caller's PARTIR_SUM_FUSED: every output is one accumulator over all K, so
 // neither K parts nor a split last wave.
 bool gemm_one_accumulator(const GemmSpec& g) { return g.rk > 1 && g.sum_impl == PARTIR_SUM_FUSED; }
@@ -233,8 +236,11 @@ GemmTiling gemm_tiling(const GemmSpec& g) {
   best.ks = g.K;
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return best;   // nothing to launch
   const int64_t nk = cdiv(g.K, 64);
-  const bool shard_parts = g.rk > 1 && g.sum_impl == PARTIR_SUM_SPLITK;   // one partial per #sum shard
-  // a product without a #sum whose output is one 256-wide tile needs no workspace
+  const bool shard_parts = gemm_shard_parts(g);
+  // A product without a #sum whose output is one 256-wide tile keeps to one
+  // accumulator: it has always been callable without a workspace.  What that
+  // costs (256 x 256 x K, one accumulator / 4 parts, us): K 2048 10.7 / 11.2,
+  // 4096 18.3 / 11.0, 16384 62 / 21, 65536 240 / 66.
   const bool may_split = g.split_ok && !gemm_one_accumulator(g) && (g.rk > 1 || gemm_tiles(g, 256) > 1);
   double best_us = 0;
   for (int tile = 256; tile >= 64; tile /= 2) {
@@ -308,6 +314,7 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
   const GemmTiling c = bf16 ? gemm_tiling(g) : GemmTiling{};
   const bool split = bf16 ? c.parts > 1 : gemm_uses_splitk(g);
   const int nparts = bf16 ? c.parts : (split ? g.rk : 1);
+  const bool k_parts = bf16 && split && !gemm_shard_parts(g);   // the planner's K ranges, not the shards'
   if (g.rk > 1) {
     plan.n_sum_loops += 1;
     if (split) plan.n_sum_splitk += 1;
@@ -350,9 +357,9 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     L.text = describe_gemm(g, p.tail_parts > 1 ? tail_base + (ntiles - tail_base) * p.tail_parts : ntiles * p.nsplit,
                            split);
     char buf[200];
-    if (split && g.sum_impl != PARTIR_SUM_SPLITK) {   // counted in 256 x 256 output tiles, like the tail split
-      textf(buf, sizeof buf, "; the last %lld tiles as %d K parts of %lld K tiles each",
-               (long long)gemm_tiles(g, 256), c.parts, (long long)(c.ks / 64));
+    if (k_parts) {
+      textf(buf, sizeof buf, "; %lld tiles as %d K parts of %lld K tiles each", (long long)ntiles, c.parts,
+               (long long)(c.ks / 64));
       L.text += buf;
     }
     if (c.tile != 256) {
@@ -397,7 +404,7 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
   if (split) {
     Launch R;
     R.kind = L_REDUCE;
-    R.name = std::string(g.name) + (g.rk > 1 ? ".reduce" : ".fixup");
+    R.name = std::string(g.name) + ".reduce";
     ReduceParams& r = R.reduce;
     r.partial = (const float*)ws;
     r.part_ld = g.N; r.part_stride = g.M * g.N;
@@ -409,13 +416,13 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     r.out_bf16 = (!g.resid_add && g.c_dtype == PARTIR_BF16);
     r.resid_add = g.resid_add;
     char buf[256];
-    if (g.rk > 1)
+    if (k_parts)
+      textf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum of the %d K parts in ascending order, then the epilogue",
+               (long long)g.M, (long long)g.N, nparts);
+    else
       textf(buf, sizeof buf, "splitk_reduce: C[%lld,%lld] = sum_{r=0..%d} partial[r] (in-device all_reduce)%s%s",
                (long long)g.M, (long long)g.N, nparts - 1, g.bias[0] ? " + bias" : "",
                g.resid_add ? " + residual" : "");
-    else
-      textf(buf, sizeof buf, "%s: C[%lld,%lld] = sum of the %d K parts in ascending order, then the epilogue",
-               R.name.c_str(), (long long)g.M, (long long)g.N, nparts);
     R.text = buf;
     plan.launches.push_back(R);
     return 2;

@@ -601,9 +601,9 @@ def test_decoder_sharded_plan():
     (8192, 15360, 5120, 128, 2),   # 1920 tiles
     (8192, 4096, 4096, 0, 1),      # 512 tiles: whole waves
     (8192, 13824, 4096, 0, 1),     # 1728 tiles: 192 left over, 2 x 192 would not fit one wave
-    (512, 512, 4096, 4, 4),        # 4 tiles, 64 K tiles: 4 quarters of K each
+    (8192, 4352, 4096, 32, 4),     # 544 tiles: 32 left over, 64 K tiles: 4 quarters of K each
     (512, 512, 256, 0, 1),         # 4 K tiles: too short to split
-    (256, 256, 4096, 0, 1),        # 1 tile: 4 parts would not fill the 8 XCDs evenly
+    (256, 256, 4096, 0, 1),        # one 256-wide tile: no workspace, whatever tile runs it
 ])
 def test_last_wave_tail_split(M, N, K, tail, parts):
     """The load-balancing split of the last partial wave of output tiles:

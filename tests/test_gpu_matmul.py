@@ -218,27 +218,26 @@ def test_degenerate_shard_sizes(dtype):
 
 
 # ---------------------------------------------------------------------------
-# The last, partial wave of output tiles split into K parts (load balance):
-# 1000 x 304 outputs are 8 tiles of 256 x 256 (16 with #tile N x4), each run
-# as 4 workgroups over 17 + 17 + 17 + 14 of the 65 K tiles (K = 4112: the
-# last K tile holds 16 columns); a fixup launch adds the parts in order.
+# K parts of a short grid: 1000 x 304 outputs are 80 tiles of 64 x 64, each run
+# as 4 workgroups over 17 + 17 + 17 + 14 of the 65 K tiles (K = 4112: the last
+# K tile holds 16 columns) into fp32 partials that a reduction adds in order.
 @pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("tile,summ,R", [(None, None, 1), ("M", None, 4), ("N", None, 4), (None, "K", 2),
                                          ("M", "K", 2)])
-def test_bf16_last_wave_split_ragged(tile, summ, R, out):
+def test_bf16_k_parts_ragged(tile, summ, R, out):
     M, N, K = 1000, 304, 4112
     plan = P.plan_loop_matmul(M, N, K, ab=P.BF16, c=P.F32 if out == torch.float32 else P.BF16,
-                              tile=tile, sum=summ, R=R, sum_impl=P.SUM_AUTO)
-    assert "K parts of 17 K tiles" in plan["text"], plan["text"]
+                              tile=tile, sum=summ, R=R)
+    assert "80 tiles as 4 K parts of 17 K tiles" in plan["text"], plan["text"]
     A = I.gaussian(121, 0, (M, K), 1.0, "bf16")
     B = I.gaussian(121, 1, (K, N), K ** -0.5, "bf16")
-    say(f"bf16 last-wave split {M}x{N}x{K} tile={tile} sum={summ} R={R} out={out}")
+    say(f"bf16 K parts {M}x{N}x{K} tile={tile} sum={summ} R={R} out={out}")
     C = run(A, B, tile, summ, R, "nk", out_dtype=out)
     err = check(A, B, C, tile, summ, R, TOL_BF16)
     assert err <= accum_bound(K) + (2.0 ** -8 if out == torch.bfloat16 else 0.0)
 
 
-def test_last_wave_split_integer_exact_and_deterministic():
+def test_k_parts_integer_exact_and_deterministic():
     """Small-integer inputs: every partial and their sum are exact in fp32, so
     the split tiles equal the oracle bit for bit; repeated calls agree."""
     M, N, K = 1000, 304, 4112
@@ -248,6 +247,52 @@ def test_last_wave_split_integer_exact_and_deterministic():
     c1 = run(A, B, "M", None, 4, "nk", out_dtype=torch.float32)
     c2 = run(A, B, "M", None, 4, "nk", out_dtype=torch.float32)
     assert np.array_equal(host(c1), ref) and torch.equal(c1, c2)
+
+
+# ---------------------------------------------------------------------------
+# The last, partial wave of 256-wide tiles split into K parts (load balance):
+# 4000 x 4360 outputs are 288 ragged tiles, the last 32 of them run as 4
+# workgroups each over 21 + 21 + 21 + 18 of the 81 K tiles (K = 5168: the last
+# K tile holds 48 columns); a fixup launch adds the parts in order.
+TAIL = (4000, 4360, 5168)
+
+
+def tail_rows():
+    """Rows of the split tiles (the last four tile rows) and some before them."""
+    M = TAIL[0]
+    return sorted({0, 255, 256, M - 1} | {256 * t + (37 * t) % 160 for t in range(16)} |
+                  set(range(3072, M, 97)))
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("tile,summ,R", [(None, None, 1), ("M", None, 4), ("N", None, 5), (None, "K", 2),
+                                         ("M", "K", 2)])
+def test_bf16_last_wave_split_ragged(tile, summ, R, out, layout):
+    M, N, K = TAIL
+    plan = P.plan_loop_matmul(M, N, K, ab=P.BF16, c=P.F32 if out == torch.float32 else P.BF16,
+                              b_layout=P.B_NK if layout == "nk" else P.B_KN, tile=tile, sum=summ, R=R)
+    assert "the last 32 tiles as 4 K parts of 21 K tiles" in plan["text"] and ".fixup:" in plan["text"], plan["text"]
+    A = I.gaussian(127, 0, (M, K), 1.0, "bf16")
+    B = I.gaussian(127, 1, (K, N), K ** -0.5, "bf16")
+    say(f"bf16 last-wave split {M}x{N}x{K} tile={tile} sum={summ} R={R} {layout} out={out}")
+    rows = tail_rows()
+    C = host(run(A, B, tile, summ, R, layout, out_dtype=out))[rows]
+    Ar = A.f64()[rows]
+    err = O.normalised_error(C, O.matmul(Ar, B.f64()), O.abs_product(Ar, B.f64()))
+    say(f"    {len(rows)} rows, max normalised error {err:.3e}")
+    assert err <= accum_bound(K) + (2.0 ** -8 if out == torch.bfloat16 else 0.0)
+
+
+def test_last_wave_split_integer_exact_and_deterministic():
+    """As above with small integers, bit for bit, and twice alike."""
+    M, N, K = TAIL
+    A = I.small_ints(128, 0, (M, K), dtype="bf16")
+    B = I.small_ints(128, 1, (K, N), dtype="bf16")
+    c1 = run(A, B, "M", None, 4, "nk", out_dtype=torch.float32)
+    c2 = run(A, B, "M", None, 4, "kn", out_dtype=torch.float32)
+    rows = tail_rows()
+    assert np.array_equal(host(c1)[rows], O.matmul(A.f64()[rows], B.f64())) and torch.equal(c1, c2)
 
 
 def test_last_wave_split_full_size_sampled_rows():
@@ -286,7 +331,7 @@ def test_bf16_b_kn_modes_ragged(tile, summ, R, out):
 
 def test_bf16_b_kn_integer_exact_and_layouts_agree():
     """Small integers: B as [K, N] and as B^T [N, K] both give the exact
-    product, bit for bit; also through the last-wave split (K = 4160)."""
+    product, bit for bit; also in K parts (K = 4160)."""
     for M, N, K in [(320, 272, 512), (1000, 320, 4160)]:
         A = I.small_ints(125, 0, (M, K), dtype="bf16")
         B = I.small_ints(125, 1, (K, N), dtype="bf16")

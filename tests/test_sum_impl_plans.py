@@ -27,6 +27,25 @@ def test_split_is_one_partial_per_shard():
         assert "sum_{r=0..2} partial[r]" in p["text"]
 
 
+@pytest.mark.parametrize("M,N,K,tiles,edge,parts,kt", [
+    (512, 512, 4096, 64, 64, 4, 16),
+    (300, 520, 4104, 45, 64, 4, 17),
+    (200, 4096, 16384, 64, 128, 4, 64),
+])
+@pytest.mark.parametrize("R", [1, 8])
+def test_k_parts_are_counted_in_the_tiles_that_run(M, N, K, tiles, edge, parts, kt, R):
+    """A short grid: every output tile in K parts whose fp32 partials a
+    reduction adds, with or without a #sum."""
+    R = R if K % (8 * R) == 0 else 3
+    p = P.plan_loop_matmul(M, N, K, sum="K" if R > 1 else None, R=R)
+    t = p["text"]
+    assert f"; {tiles} tiles as {parts} K parts of {kt} K tiles each; workgroup tiles of {edge} x {edge}" in t, t
+    assert f"grid {tiles * parts} WGs" in t and "the last" not in t and ".fixup" not in t
+    assert f"splitk_reduce: C[{M},{N}] = sum of the {parts} K parts in ascending order" in t
+    assert p["n_launches"] == 2 and p["n_sum_splitk"] == (R > 1)
+    assert p["workspace_bytes"] >= parts * M * N * 4
+
+
 def test_fused_says_nothing_about_a_product_without_a_sum():
     a, f = (P.plan_loop_matmul(304, 520, 4104, tile="M", R=2, sum_impl=i) for i in (P.SUM_AUTO, P.SUM_FUSED))
     assert a["text"] == f["text"] and a["n_launches"] == 2
