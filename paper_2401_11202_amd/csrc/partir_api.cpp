@@ -152,6 +152,7 @@ struct GemmSpec {
   void* aux = nullptr;          // bf16 pre-activation output (kept for a backward pass)
   bool tail_ok = false;         // the caller's workspace region holds gemm_ws_bytes (tail split allowed)
   bool split_ok = false;        // ... and one plain C (and residual) takes the ordered reduction of K parts
+  bool parts = false;           // operands in device-local arrays
   bool a_mn = false;            // bf16 A stored [K, M] (leading dim lda) instead of [M, K]
   const char* name = "gemm";    // role, used as the trace name
   const char* label = "gemm";   // loop nest, for the plan text
@@ -207,27 +208,47 @@ struct GemmTiling {
   int64_t ks = 0;    // K extent of a part
 };
 
-// Time of a bf16 product in microseconds, from the tiles a CU runs one after
-// the other (n) and the 64-wide K tiles of each (nk).  The constants are
-// fitted to measurements (n x nk: us of the launch):
-//   tile 256  1 x 64: 95, 1 x 40: 62, 1 x 32: 53, 2 x 24: 89   one workgroup a CU
-//   tile 128  1 x 32: 22, 1 x 64: 36, 1 x 128: 72, 3 x 32: 54, 4 x 64: 119
-//             (two at a time; an odd last one alone)
-//   tile 64   1 x 16: 10, 1 x 256: 73, 4 x 32: 33
-// A 256 tile does the most work per byte moved through LDS (1450 TFLOP/s on
-// full waves against 1200 and 700), so the small tiles pay where its grid
-// leaves CUs idle.  A K split adds the partials' traffic and a launch.
+// Time of a bf16 product in microseconds, from the rounds of tiles on the CUs
+// and the 64-wide K tiles of each (nk): what ranks the tiles and K parts.  A
+// CU holds one 256-wide tile, one 128-wide tile on a grid of at most one a CU,
+// else two at a time; a round that is not full is shorter.  Measured (us of
+// the launch in 256 / 128 / 64 wide tiles):
+//   1166 x 2768 x 1672 (0.2 rounds of 256)          35 /  20 /  32
+//   2261 x 7072 x 2512 (1)                          66 /  93 / 160
+//   5308 x 3296 x 5584 (1.07)                      234 / 257 / 394
+//   4457 x 4440 x 3816 (1.3)                       158 / 194 / 322
+//   3183 x 7184 x 2480 (1.5)                       116 / 134 / 220
+//   3279 x 10544 x 80 (2.1)                         33 /  26 /  49
+// The constants rank best over 1835 random products of 12 us and more (three
+// layouts, fp32 and bf16 outputs) and 2945 products of the blocks: the choice
+// is 1.1% (0.3% in blocks) above the best measured one on average.  Without
+// the shorter last round and with 2 + 0.87 nk for a pair it was 2.8%, and
+// 128-wide tiles were taken where 256-wide ones are up to 37% faster (a little
+// over one round of 256, or over two of 128).  Device-local arrays keep whole
+// rounds: with the shorter last one their calls were 1.8% slower where the
+// choice changed, without it 0.8% faster.  A fixup that also adds a residual
+// costs the same for few tiles as for many (22 of 1152 x 1024 x 10240 in 4
+// parts: 114 against 67 in 64-wide tiles).  A K split adds the partials'
+// traffic and a launch.
 double gemm_us(const GemmSpec& g, int tile, int parts) {
   const int64_t nk = cdiv(cdiv(g.K, 64), parts);
   const int64_t units = gemm_tiles(g, tile) * parts;
-  const double n = (double)cdiv(units, kNumCU);
+  const double n = (double)cdiv(units, kNumCU), fill = (double)units / kNumCU - (n - 1);   // rounds; of the last one
   double t;
   int64_t base;
   const int tail = tile == 256 && parts == 1 ? gemm_tail_parts(g, &base) : 1;
-  if (tile == 256) t = 3 + (tail > 1 ? n - 1 + 1.0 / tail : n) * (6 + 1.38 * nk) + (tail > 1 ? 5 + 10 * tail : 0);
-  else if (tile == 128) t = 5 + std::floor(n / 2) * (2 + 0.87 * nk) + (std::fmod(n, 2) > 0 ? 1 + 0.52 * nk : 0);
-  else t = 5 + std::max(0.27 * nk, n * (0.5 + 0.2 * nk));
-  if (parts > 1) t += 5 + 8.0 * parts * g.M * g.N / 5.5e6;   // 5.5 MB/us, written and read
+  if (tile == 256) {
+    const double last = tail > 1 ? 1.0 / tail : (g.parts ? 1.0 : 0.73 + 0.27 * fill);
+    const double fixup = tail > 1 ? 5 + 10.7 * tail * (g.resid_add ? 1.0 : std::min(1.0, fill * tail)) : 0;
+    t = 3 + (n - 1 + last) * (6 + 1.38 * nk) + fixup;
+  } else if (tile == 128) {
+    const double pair = 1.32 + (g.a_mn || g.parts ? 0.85 : 0.91) * nk, pairs = (double)units / (2 * kNumCU);
+    const double whole = std::floor(pairs), rest = pairs - whole;
+    t = 5 + (units <= kNumCU ? 1 + 0.52 * nk : pair * (whole + (rest > 0 ? std::min(1.0, 0.6 + 0.7 * rest) : 0)));
+  } else {
+    t = 5 + std::max(0.27 * nk, n * (0.4 + 0.225 * nk));
+  }
+  if (parts > 1) t += 5.2 + 5.8 * parts * g.M * g.N / 5.5e6;   // 5.5 MB/us
   return t;
 }
 
@@ -1229,7 +1250,7 @@ void plan_attn_block_bwd(const AttnBlockBwdArgs& a, void* ws, Plan& plan) {
   // over the three weights, read through a table of three K parts (whole-K
   // accumulation in q, k, v order)
   GemmSpec gx;
-  gx.A = dQKV; gx.C[0] = a.dX;
+  gx.A = dQKV; gx.C[0] = a.dX; gx.parts = true;
   gx.lda = 3 * D; gx.ldb = D; gx.ldc = D; gx.M = T; gx.N = D; gx.K = 3 * D;
   gx.c_dtype = PARTIR_F32; gx.rm = a.Rb; gx.tail_ok = true;
   gx.name = "attn.bwd.dx"; gx.label = "bwd.dx dX = sum over m and q|k|v of dQKV[b][:, m] . W{q,k,v}[:, m]^T";
@@ -1640,7 +1661,7 @@ void plan_mlp_sharded(const MlpShardedArgs& a, void* ws, Plan& plan) {
   };
   GemmSpec g1;
   g1.A = nullptr; g1.B[0] = nullptr; g1.C[0] = H; g1.bias[0] = (const float*)a.b1;
-  g1.lda = D; g1.ldb = D / a.Rb; g1.ldc = F;
+  g1.lda = D; g1.ldb = D / a.Rb; g1.ldc = F; g1.parts = true;
   g1.M = T; g1.N = F; g1.K = D;
   g1.c_dtype = PARTIR_BF16; g1.rm = a.Rb; g1.rn = a.Rm; g1.act = a.act;
   g1.name = "mlp.up";
@@ -1657,7 +1678,7 @@ void plan_mlp_sharded(const MlpShardedArgs& a, void* ws, Plan& plan) {
   parted(g1, t1, "; X rows and W1 blocks read from each device's array (fused all_gathers)");
   GemmSpec g2;
   g2.A = H; g2.B[0] = nullptr; g2.C[0] = nullptr; g2.bias[0] = (const float*)a.b2;
-  g2.lda = F; g2.ldb = F / a.Rm; g2.ldc = D;
+  g2.lda = F; g2.ldb = F / a.Rm; g2.ldc = D; g2.parts = true;
   g2.M = T; g2.N = D; g2.K = F;
   g2.c_dtype = a.out; g2.rm = a.Rb; g2.rk = a.Rm;
   g2.name = "mlp.down";
@@ -1750,22 +1771,23 @@ void plan_dec_sharded(const DecShardedArgs& a, void* ws, Plan& plan) {
   GemmSpec gq;
   gq.A = xn;
   for (int i = 0; i < 3; ++i) gq.C[i] = qkvo ? qkvo + i * one : nullptr;
-  gq.ngroups = 3;
+  gq.ngroups = 3; gq.parts = true;
   gq.lda = D; gq.ldb = D / a.Rb; gq.ldc = D; gq.M = T; gq.N = D; gq.K = D;
   gq.c_dtype = PARTIR_BF16; gq.rm = a.Rb; gq.rn = a.Rm; gq.tail_ok = true;
   gq.name = "attn.qkv"; gq.label = "attn.qkv Q|K|V = xn[b] . all_gather<B>(W{q,k,v})[:, m]";
   GemmSpec go;
-  go.A = qkvo ? qkvo + 3 * one : nullptr; go.resid_add = true;
+  go.A = qkvo ? qkvo + 3 * one : nullptr; go.resid_add = true; go.parts = true;
   go.lda = D; go.ldb = D / a.Rm; go.ldc = D; go.M = T; go.N = D; go.K = D;
   go.c_dtype = PARTIR_F32; go.rm = a.Rb; go.rk = a.Rm; go.tail_ok = true;
   go.name = "attn.out"; go.label = "dec.attn_out x_bm += reduce_scatter<M>(sum_m O[:, m] . all_gather<B>(Wo)[m])";
   GemmSpec g1;
   g1.A = xn; g1.C[0] = Hf;
+  g1.parts = true;
   g1.lda = D; g1.ldb = D / a.Rb; g1.ldc = F; g1.M = T; g1.N = F; g1.K = D;
   g1.c_dtype = PARTIR_BF16; g1.rm = a.Rb; g1.rn = a.Rm; g1.act = 1;
   g1.name = "mlp.up"; g1.label = "dec.ffn_up H = gelu(hn[b] . all_gather<B>(W1)[:, m])";
   GemmSpec g2;
-  g2.A = Hf; g2.resid_add = true;
+  g2.A = Hf; g2.resid_add = true; g2.parts = true;
   g2.lda = F; g2.ldb = F / a.Rm; g2.ldc = D; g2.M = T; g2.N = D; g2.K = F;
   g2.c_dtype = PARTIR_F32; g2.rm = a.Rb; g2.rk = a.Rm; g2.tail_ok = true;
   g2.name = "mlp.down"; g2.label = "dec.ffn_down x_bm += reduce_scatter<M>(sum_m H[:, m] . all_gather<B>(W2)[m])";

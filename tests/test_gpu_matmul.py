@@ -218,17 +218,17 @@ def test_degenerate_shard_sizes(dtype):
 
 
 # ---------------------------------------------------------------------------
-# K parts of a short grid: 1000 x 304 outputs are 80 tiles of 64 x 64, each run
-# as 4 workgroups over 17 + 17 + 17 + 14 of the 65 K tiles (K = 4112: the last
+# K parts of a short grid: 600 x 304 outputs are 50 tiles of 64 x 64, each run
+# as 4 workgroups over 33 + 33 + 33 + 30 of the 129 K tiles (K = 8208: the last
 # K tile holds 16 columns) into fp32 partials that a reduction adds in order.
 @pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("tile,summ,R", [(None, None, 1), ("M", None, 4), ("N", None, 4), (None, "K", 2),
                                          ("M", "K", 2)])
 def test_bf16_k_parts_ragged(tile, summ, R, out):
-    M, N, K = 1000, 304, 4112
+    M, N, K = 600, 304, 8208
     plan = P.plan_loop_matmul(M, N, K, ab=P.BF16, c=P.F32 if out == torch.float32 else P.BF16,
                               tile=tile, sum=summ, R=R)
-    assert "80 tiles as 4 K parts of 17 K tiles" in plan["text"], plan["text"]
+    assert "50 tiles as 4 K parts of 33 K tiles" in plan["text"], plan["text"]
     A = I.gaussian(121, 0, (M, K), 1.0, "bf16")
     B = I.gaussian(121, 1, (K, N), K ** -0.5, "bf16")
     say(f"bf16 K parts {M}x{N}x{K} tile={tile} sum={summ} R={R} out={out}")
@@ -240,7 +240,7 @@ def test_bf16_k_parts_ragged(tile, summ, R, out):
 def test_k_parts_integer_exact_and_deterministic():
     """Small-integer inputs: every partial and their sum are exact in fp32, so
     the split tiles equal the oracle bit for bit; repeated calls agree."""
-    M, N, K = 1000, 304, 4112
+    M, N, K = 600, 304, 8208
     A = I.small_ints(122, 0, (M, K), dtype="bf16")
     B = I.small_ints(122, 1, (K, N), dtype="bf16")
     ref = O.matmul(A.f64(), B.f64())

@@ -47,7 +47,7 @@ def test_ragged_products(M, N, K, words, layout):
 
 
 @pytest.mark.parametrize("layout", ["kn", "nk"])
-@pytest.mark.parametrize("rows", [60, 200, 900])
+@pytest.mark.parametrize("rows", [60, 200, 900, 1700])
 def test_small_tiles_give_the_bits_of_the_large_ones(rows, layout):
     """Without a K split every tile size forms an output's sum in the same
     order: the first rows of a product computed alone (64- or 128-wide tiles)
