@@ -2,8 +2,9 @@
 // [M, K], B row-major [K, N] or given by its transpose [N, K].
 //
 // 128x128 or 64x64 output tile per workgroup, four waves (2 x 2) of 64x64 or
-// 32x32.  K advances in 32-wide tiles through NS LDS stages that buffer loads
-// write directly; the pipeline is that of the bf16 tile kernel (one barrier
+// 32x32.  K advances in 32-wide tiles through NS = 2 LDS stages that buffer
+// loads write directly (four hold a CU to two workgroups: 1000 x 600 in 8 shards
+// of 128 27.9 us against 26.4, 1961 x 1776 x 2176 143 against 136); the pipeline is that of the bf16 tile kernel (one barrier
 // per K tile, before its last step, after which the stage is refilled and the
 // next tile's first fragments are read).  A #sum runs in one accumulator over
 // all K or as one fp32 partial per K range.
@@ -15,8 +16,8 @@
 //
 // Bound by the matrix cores (157 TFLOP/s): 64 cycles per MFMA against 16 bytes
 // of LDS reads per lane and four MFMAs.  Against one 32x32 accumulator a wave
-// over a single register-staged LDS buffer (the long-rows kernel below, which
-// used to run every size): 1800 x 2056 x 2048 204 -> 126 us (74 -> 120 TFLOP/s),
+// over a single register-staged LDS buffer (the staged kernel below, which used
+// to run every size): 1800 x 2056 x 2048 204 -> 126 us (74 -> 120 TFLOP/s),
 // 4096^3 at 144 TFLOP/s.
 #include "kernels.h"
 #include "lds_dma.h"
@@ -30,7 +31,7 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 32, NT = 256, KK = BK / 8;
+constexpr int BK = 32, NT = 256, KK = BK / 8, NS = 2;
 constexpr uint32_t OOB = 0x80000000u;          // offset that reads as zero
 
 // K-contiguous tile: 128-byte rows of eight 16-byte chunks, chunk c of row r
@@ -50,7 +51,7 @@ __device__ __forceinline__ int kn_swz(int r) { return 8 * ((r >> 2) & 1); }
 __device__ __forceinline__ f32x4 lds_read4(const char* __restrict__ p) { return *(const f32x4*)p; }
 __device__ __forceinline__ float lds_read1(const char* __restrict__ p) { return *(const float*)p; }
 
-template <int BT, int NS, int BKN>
+template <int BT, int BKN>
 __device__ __forceinline__ void gemm_f32_body(const GemmF32Params& p) {
   constexpr int WT = BT / 2, NB = WT / 32;         // a wave's part of the tile, in 32-wide blocks
   constexpr int OP = BT * BK * 4, STAGE = 2 * OP;
@@ -229,14 +230,15 @@ __device__ __forceinline__ void gemm_f32_body(const GemmF32Params& p) {
     }
 }
 
-template <int BT, int NS, int BKN>
-__global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmF32Params p) { gemm_f32_body<BT, NS, BKN>(p); }
+template <int BT, int BKN>
+__global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmF32Params p) { gemm_f32_body<BT, BKN>(p); }
 
 // Any leading dimension (64-bit addresses; the kernel above bounds its loads
-// by 32-bit byte ranges): 64x64 tiles, K in steps of 16 through one LDS
-// buffer, register-staged.
+// by 32-bit byte ranges), and a short K on many workgroups (the planner says
+// where the line lies): 64x64 tiles, K in steps of 16 through one LDS buffer,
+// register-staged.
 constexpr int LT = 64, LBK = 16, PAD = 4;
-__global__ __launch_bounds__(NT) void gemm_f32_long_rows_kernel(GemmF32Params p) {
+__global__ __launch_bounds__(NT) void gemm_f32_staged_kernel(GemmF32Params p) {
   __shared__ float As[LBK][LT + PAD];
   __shared__ float Bs[LBK][LT + PAD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -292,10 +294,10 @@ __global__ __launch_bounds__(NT) void gemm_f32_long_rows_kernel(GemmF32Params p)
   }
 }
 
-template <int BT, int NS>
+template <int BT>
 void launch(const GemmF32Params& p, dim3 grid, hipStream_t s) {
-  if (p.b_nk) hipLaunchKernelGGL((gemm_f32_kernel<BT, NS, 0>), grid, dim3(NT), 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<BT, NS, 1>), grid, dim3(NT), 0, s, p);
+  if (p.b_nk) hipLaunchKernelGGL((gemm_f32_kernel<BT, 0>), grid, dim3(NT), 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<BT, 1>), grid, dim3(NT), 0, s, p);
 }
 
 constexpr int64_t kMaxLd = (int64_t)1 << 24;   // 32 rows (or k rows) within a 2^31-byte range
@@ -308,13 +310,13 @@ hipError_t launch_gemm_f32(const GemmF32Params& p, hipStream_t s) {
   const int64_t nwg = (int64_t)p.tiles_m * p.tiles_n * p.nsplit;
   if (nwg <= 0 || nwg >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)nwg);
-  if (p.lda > kMaxLd || p.ldb > kMaxLd) {
-    if (p.tile != LT) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gemm_f32_long_rows_kernel, grid, dim3(NT), 0, s, p);
+  if (p.staged ? p.tile != LT : (p.lda > kMaxLd || p.ldb > kMaxLd)) return hipErrorInvalidValue;
+  if (p.staged) {
+    hipLaunchKernelGGL(gemm_f32_staged_kernel, grid, dim3(NT), 0, s, p);
   } else if (p.tile == 128) {
-    launch<128, 2>(p, grid, s);
+    launch<128>(p, grid, s);
   } else if (p.tile == 64) {
-    launch<64, 4>(p, grid, s);
+    launch<64>(p, grid, s);
   } else {
     return hipErrorInvalidValue;
   }

@@ -97,7 +97,8 @@ struct GemmF32Params {
   int64_t lda, ldb, ldc, part_stride;
   int M, N, K;
   int b_nk;
-  int tile;          // output tile edge: 128 or 64 (64 with a leading dim above 2^24)
+  int tile;          // output tile edge: 128 or 64
+  int staged;        // the register-staged kernel (tile 64; any leading dim, the others at most 2^24)
   int tiles_m, tiles_n;
   int ks;            // K extent of a part
   int nsplit;

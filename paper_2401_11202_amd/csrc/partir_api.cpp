@@ -283,16 +283,33 @@ GemmTiling gemm_tiling(const GemmSpec& g) {
   return best;
 }
 
-// Output tile of an fp32 product.  Per 32-wide K tile a CU takes 1.95 us for a
-// 128-wide tile and 0.55 us for a 64-wide one (measured: 4096^3 955 / 1009 us,
-// 1800 x 2056 x 2048 134 / 150, 2900^3 514 / 431, 333 x 2500 x 3000 180 / 57):
-// the larger tile wherever its whole waves are not mostly idle.
-int gemm_f32_tiling(const GemmSpec& g, int nsplit) {
+// How an fp32 product runs: the output tile, and whether by the
+// register-staged kernel.
+struct F32Tiling {
+  int tile = 64;
+  bool staged = false;
+};
+
+// Per 32-wide K tile a CU takes 1.95 us for a 128-wide tile and 0.55 us for a
+// 64-wide one (measured: 4096^3 955 / 1009 us, 1800 x 2056 x 2048 126 / 150,
+// 2900^3 514 / 431, 333 x 2500 x 3000 180 / 57): the larger tile wherever its
+// whole waves are not mostly idle.  A short K on many workgroups goes to the
+// register-staged kernel, which has no pipeline to fill, holds more workgroups
+// a CU and pads K to 16 only (us, pipelined / register-staged: 2173 x 408 in 8
+// shards of 48 26.3 / 22.1, 1921 x 2280 x 80 14.2 / 13.0, 941 x 728 in 8 of 88
+// 25.4 / 24.4; 1255 x 2576 x 120 14.1 / 15.8; 1.2 workgroups a CU and 72 11.8 /
+// 12.1), except where 128-wide tiles fill their rounds (2955 x 2480 x 64 16.7 /
+// 16.1) and no partials are written (2493 x 328 in 8 shards of 64 27.4 / 23.5).
+F32Tiling gemm_f32_tiling(const GemmSpec& g, int nsplit) {
   constexpr int64_t kMaxLd = (int64_t)1 << 24;   // the tiles' loads are bounded by 32-bit byte ranges
-  if (g.lda > kMaxLd || g.ldb > kMaxLd) return 64;
-  const double n64 = std::max(1.0, (double)(gemm_tiles(g, 64) * nsplit) / kNumCU);
+  constexpr int64_t kShortK = 112;
+  const double n64 = (double)(gemm_tiles(g, 64) * nsplit) / kNumCU;
+  const int64_t k = nsplit > 1 ? g.K / g.rk : g.K;
+  if (g.lda > kMaxLd || g.ldb > kMaxLd) return {64, true};
   const int64_t n128 = cdiv(gemm_tiles(g, 128) * nsplit, kNumCU);
-  return 1.95 * n128 <= 0.55 * n64 ? 128 : 64;
+  const bool wide = 1.95 * n128 <= 0.55 * std::max(1.0, n64);
+  if (k <= kShortK && n64 > 2.5 && (!wide || nsplit > 1)) return {64, true};
+  return {wide ? 128 : 64, false};
 }
 
 // Workspace of one GEMM: split-K partials, or the tail parts of 256-wide tiles.
@@ -402,8 +419,10 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
       return 2;
     }
   } else {
-    const int tile = gemm_f32_tiling(g, nparts);
+    const F32Tiling ft = gemm_f32_tiling(g, nparts);
+    const int tile = ft.tile;
     GemmF32Params& p = L.gemm32;
+    p.staged = ft.staged;
     p.A = (const float*)g.A;
     p.B = (const float*)g.B[0];
     p.C = split ? (float*)ws : (float*)g.C[0];
@@ -419,7 +438,7 @@ int plan_gemm(const GemmSpec& g, void* ws, Plan& plan) {
     L.kind = L_GEMM_F32;
     L.name = g.name;
     L.text = describe_gemm(g, (int64_t)p.tiles_m * p.tiles_n * p.nsplit, split);
-    if (g_want_text) L.text += "; workgroup tiles of " + std::to_string(tile);
+    if (g_want_text) L.text += "; workgroup tiles of " + std::to_string(tile) + (ft.staged ? ", register-staged" : "");
   }
   plan.launches.push_back(L);
   if (split) {

@@ -32,6 +32,27 @@ def test_ragged_products(M, N, K, tile, layout):
     assert torch.all(big[M:] == 7.25) and torch.all(big[:, N:] == 7.25)
 
 
+# a short K on many workgroups: one K step of 16, parts of one, the longest and
+# one past it, with and without a #sum
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("M,N,K,R", [(1299, 2004, 4, 1), (1299, 2004, 112, 1), (1299, 2004, 116, 1), (899, 732, 96, 8),
+                                     (2173, 408, 384, 8)])
+def test_short_contractions(M, N, K, R, layout):
+    A = I.gaussian(213, 0, (M, K), 1.0, "f32")
+    B = I.gaussian(213, 1, (K, N), K ** -0.5, "f32")
+    summ = "K" if R > 1 else None
+    text = P.plan_loop_matmul(M, N, K, ab=P.F32, b_layout=P.B_KN if layout == "kn" else P.B_NK, sum=summ, R=R)["text"]
+    assert ("register-staged" in text) == (K // R <= 112), text
+    say(f"f32 short K {M}x{N}x{K} R={R} {layout}")
+    big = torch.full((M + 4, N + 8), 7.25, dtype=torch.float32, device="cuda")
+    Bd = (B if layout == "kn" else I.transposed(B)).to_device()
+    P.loop_matmul(A.to_device(), Bd, sum=summ, R=R, b_layout=layout, out=big[:M, :N])
+    torch.cuda.synchronize()
+    ref, norm = O.matmul(A.f64(), B.f64()), O.abs_product(A.f64(), B.f64())
+    assert O.normalised_error(host(big[:M, :N]), ref, norm) <= accum_bound(K)
+    assert torch.all(big[M:] == 7.25) and torch.all(big[:, N:] == 7.25)
+
+
 @pytest.mark.parametrize("summ,R,impl", [(None, 1, "auto"), ("K", 5, "splitk"), ("K", 5, "fused")])
 def test_rows_further_apart_than_a_byte_range_holds(summ, R, impl):
     """lda = 2^24 + 4: views whose rows lie 64 MiB apart."""

@@ -34,3 +34,21 @@ def test_few_residual_tiles_are_not_tail_split():
     text = P.plan_decoder_layer_sharded(1, 1152, 1024, 8, 128, 10240, R_batch=1, R_model=2)["text"]
     down = next(l for l in text.splitlines() if "ffn_down" in l)
     assert "the last" not in down and "workgroup tiles of 64 x 64" in down, down
+
+
+@pytest.mark.parametrize("M,N,K,R,staged", [
+    (2173, 408, 384, 8, True),      # 8 shards of 48, 7.4 workgroups a CU: us pipelined / register-staged 26.3 / 22.1
+    (1070, 640, 320, 8, True),      # 23.6 / 20.9
+    (896, 728, 64, 8, True),        # 20.3 / 17.8
+    (1921, 2280, 80, 1, True),      # 14.2 / 13.0
+    (1300, 2000, 112, 1, True),     # the last short K ...
+    (1300, 2000, 116, 1, False),    # ... and past it
+    (1800, 2056, 68, 1, False),     # one round of 128-wide tiles
+    (1255, 2576, 120, 1, False),    # 14.1 / 15.8
+    (1266, 232, 288, 4, False),     # 1.2 workgroups a CU: 11.8 / 12.1
+    (256, 256, 512, 4, False),
+])
+def test_short_fp32_contractions_on_many_workgroups_are_register_staged(M, N, K, R, staged):
+    for layout in (P.B_KN, P.B_NK):
+        text = P.plan_loop_matmul(M, N, K, ab=P.F32, b_layout=layout, sum="K" if R > 1 else None, R=R)["text"]
+        assert ("tiles of 64, register-staged" in text) == staged, text
