@@ -393,8 +393,21 @@ hipError_t launch_attention_combine(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+static unsigned attention_grid(const AttnParams& p) { return (unsigned)(p.S / BQ) * p.B * p.H * p.nsplit; }
+
+AttnChoice attention_choice(const AttnParams& p, unsigned ncu) {
+  // the bounds are those of the kernel's comment
+  const unsigned nwg = attention_grid(p);
+  const int keys = p.nsplit > 1 ? p.kb_per * 64 : p.S;
+  unsigned two_groups = keys >= 512 ? ncu : 0;
+  if (p.causal && p.nsplit == 1 && keys >= 2048) two_groups = 2 * ncu;
+  if (p.causal && p.nsplit > 1 && keys >= 1536) two_groups = ncu + ncu / 2;
+  if (nwg <= two_groups) return {64, 2};
+  return {nwg < ncu ? 64 : 32, 1};
+}
+
 hipError_t launch_attention(const AttnParams& p, hipStream_t s) {
-  const unsigned nwg = (unsigned)(p.S / BQ) * p.B * p.H * p.nsplit;
+  const unsigned nwg = attention_grid(p);
   // CU count per device, looked up once (racing first calls store the same value)
   static int cus[64] = {};
   int dev = 0, ncu = 256;
@@ -405,14 +418,10 @@ hipError_t launch_attention(const AttnParams& p, hipStream_t s) {
     }
     if (cus[dev] > 0) ncu = cus[dev];
   }
-  // the bounds are those of the kernel's comment
-  const int keys = p.nsplit > 1 ? p.kb_per * 64 : p.S;
-  unsigned two_groups = keys >= 512 ? (unsigned)ncu : 0;
-  if (p.causal && p.nsplit == 1 && keys >= 2048) two_groups = 2 * (unsigned)ncu;
-  if (p.causal && p.nsplit > 1 && keys >= 1536) two_groups = (unsigned)ncu + (unsigned)ncu / 2;
-  if (nwg <= two_groups)
+  const AttnChoice c = attention_choice(p, (unsigned)ncu);
+  if (c.groups == 2)
     hipLaunchKernelGGL((attention_kernel<64, 2>), dim3(nwg), dim3(2 * NT), 0, s, p);
-  else if (nwg < (unsigned)ncu)
+  else if (c.block == 64)
     hipLaunchKernelGGL((attention_kernel<64, 1>), dim3(nwg), dim3(NT), 0, s, p);
   else
     hipLaunchKernelGGL((attention_kernel<32, 1>), dim3(nwg), dim3(NT), 0, s, p);

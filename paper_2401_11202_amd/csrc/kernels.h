@@ -147,6 +147,12 @@ struct AttnParams {
   // kept for the backward pass (written by the unsplit kernel or the combine)
   float* lse = nullptr;
 };
+// The kernel of a launch on a GPU of ncu CUs: keys per block, key groups per
+// workgroup.
+struct AttnChoice {
+  int block, groups;
+};
+AttnChoice attention_choice(const AttnParams& p, unsigned ncu);
 hipError_t launch_attention(const AttnParams& p, hipStream_t s);
 // O = combine over the shards: M = max m_s, w_s = 2^(m_s - M),
 // O = (sum_s w_s o_s) / (sum_s w_s l_s), s ascending; bf16 into p.O

@@ -854,6 +854,13 @@ GemmSpec qkv_spec(const void* Xn, const void* Wq, const void* Wk, const void* Wv
   return g;
 }
 
+// The attention kernel that the launch takes, for the plan text.
+std::string describe_attention_kernel(const AttnParams& p) {
+  if (!g_want_text) return std::string();
+  const AttnChoice c = attention_choice(p, kNumCU);
+  return "; key blocks of " + std::to_string(c.block) + (c.groups == 2 ? ", two key groups a workgroup" : "");
+}
+
 // QKV projection + attention core into (Q, K, V, O) inside the workspace;
 // `gemm_ws`: gemm_ws_bytes of the projection.
 void plan_attention_core(const void* Xn, const void* Wq, const void* Wk, const void* Wv, char* qkvo,
@@ -886,7 +893,7 @@ void plan_attention_launch(char* qkvo, int64_t B, int64_t S, int64_t D, int64_t 
   textf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads/shard) over %lld sequences x %lld heads, "
            "S=%lld, %s, %lld WGs", (long long)(H / Rm), (long long)B, (long long)H, (long long)S,
            causal ? "causal" : "full", (long long)(S / 128 * B * H));
-  L.text = buf;
+  L.text = buf + describe_attention_kernel(p);
   plan.launches.push_back(L);
 }
 
@@ -1122,7 +1129,7 @@ void plan_attn_core(const AttnCoreArgs& a, void* ws, Plan& plan) {
   textf(buf, sizeof buf, "attention: loop h [#tile<1>](%lld heads) x loop s [#sum softmax](%d key shards of %d%s) "
            "over %lld sequences, S=%lld, %s", (long long)a.H, a.Rkv, p.kb_per * 64 * parts, part, (long long)a.B,
            (long long)a.S, a.causal ? "causal" : "full");
-  L.text = buf;
+  L.text = buf + describe_attention_kernel(p);
   plan.launches.push_back(L);
   if (a.Rkv > 1) {
     Launch C = L;

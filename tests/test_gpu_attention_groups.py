@@ -14,21 +14,22 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H,R", [
-    (1, 384, 2, 1),      # one group
-    (1, 512, 2, 1),      # two groups: the first query block has one block for each
-    (1, 640, 3, 1),
-    (2, 1152, 1, 2),     # shards of 9 blocks of 64: the second group has one less
-    (1, 1024, 2, 2),     # shards past a query block, and blocks past a wave's queries
-    (1, 1024, 32, 1),    # 256 workgroups ...
-    (1, 1024, 33, 1),    # ... and 264: one group
-    (1, 1024, 64, 1),
-    (1, 1024, 65, 1),
-    (1, 2048, 32, 1),    # 512 workgroups: two groups under a causal mask only ...
-    (1, 2048, 33, 1),    # ... and 528: one group
-    (1, 3072, 8, 2),     # 384 workgroups over shards of 1536: two groups under a causal mask only
+# key groups of the launch with and without a causal mask
+@pytest.mark.parametrize("B,S,H,R,groups", [
+    (1, 384, 2, 1, (1, 1)),
+    (1, 512, 2, 1, (2, 2)),      # the first query block has one block for each group
+    (1, 640, 3, 1, (2, 2)),
+    (2, 1152, 1, 2, (2, 2)),     # shards of 9 blocks of 64: the second group has one less
+    (1, 1024, 2, 2, (2, 2)),     # shards past a query block, and blocks past a wave's queries
+    (1, 1024, 32, 1, (2, 2)),    # 256 workgroups ...
+    (1, 1024, 33, 1, (1, 1)),    # ... and 264
+    (1, 1024, 64, 1, (1, 1)),
+    (1, 1024, 65, 1, (1, 1)),
+    (1, 2048, 32, 1, (2, 1)),    # 512 workgroups ...
+    (1, 2048, 33, 1, (1, 1)),    # ... and 528
+    (1, 3072, 8, 2, (2, 1)),     # 384 workgroups over shards of 1536
 ])
-def test_key_groups(B, S, H, R, causal):
+def test_key_groups(B, S, H, R, groups, causal):
     Q, K, V = make_qkv(140 + H, B, S, H)
     rng = np.random.default_rng(140)
     rows = np.unique(np.concatenate([[b * S + r for b in range(B) for r in (0, 63, 64, 127, 128, 191, S - 1)],
@@ -36,6 +37,8 @@ def test_key_groups(B, S, H, R, causal):
     say(f"attention B={B} S={S} H={H} R_kv={R} causal={causal}")
     q, k, v = Q.to_device(), K.to_device(), V.to_device()
     o, lse = P.attention_train(q, k, v, B=B, S=S, n_heads=H, causal=causal, R_kv=R)
+    text = P.lib().partir_last_plan_text().decode()
+    assert ("two key groups" in text) == (groups[0 if causal else 1] == 2), text
     again, lse2 = P.attention_train(q, k, v, B=B, S=S, n_heads=H, causal=causal, R_kv=R)
     torch.cuda.synchronize()
     assert torch.equal(o, again) and torch.equal(lse, lse2)
