@@ -36,11 +36,6 @@ constexpr int DH = 128, BQ = 128, NT = 256;
 // 4 rows x 64 B one half of a ds_read_b64_tr_b16 touches hit all 64 banks.
 constexpr int RP = 256;
 
-// LDS reads of K fragments through a restrict pointer, for the same reason
-// as lds_read_tr16: the alias scope keeps the wait insertion from making them
-// wait on the next tiles' DMA (which writes the other stage).
-__device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { return *(const bf16x8*)p; }
-
 // KG = 1: four waves, every one over all the workgroup's keys.
 // BKV = 32: three workgroups per CU (32 KiB of LDS each, at most 168
 // VGPRs); the third wave per SIMD hides more of the load, LDS and barrier
@@ -53,14 +48,14 @@ __device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { re
 // its own, the combiner of the key shards.  A short grid is bound by its
 // longest workgroups, whose waves are one chain of S^T, exponentials and P V
 // per block: two chains a SIMD overlap, and each is half as long.  Measured
-// (1 / 2 groups, us of a pass): unsplit causal 8192 keys x 2 heads 157 / 103,
-// 4096 x 8 heads 82 / 59, 1024 x 32 heads 26 / 22, full 4096 x 8 heads 83 / 70.
+// (1 / 2 groups, us of a pass): unsplit causal 8192 keys x 2 heads 143 / 105,
+// 4096 x 8 heads 82 / 58, 1024 x 32 heads 26 / 22, full 4096 x 8 heads 82 / 67.
 // The 128 KiB hold a CU to one workgroup, so the line lies at one a CU: with a
 // second round, full masks lose (4096 x 10 heads 100 / 124, 2048 x 32 heads 70
 // / 77) and so do short shards (2 x 1024 keys, 16 heads 41 / 51).  Under a
 // causal mask the rounds even out where workgroups differ much in length, the
 // light ones filling in: unsplit from 2048 keys to two a CU (4096 x 12 heads 87 /
-// 65, 2048 x 32 52 / 47; 3072 x 24, 576 workgroups, 81 / 88), key shards of 1536
+// 63, 2048 x 32 51 / 45; 3072 x 24, 576 workgroups, 81 / 88), key shards of 1536
 // and more to one and a half (2 x 2048 keys, 5 heads 55 / 42, 2 x 4096, 3 heads
 // 98 / 75; 4 x 2048, 2 heads, 512 workgroups 60 / 74).  Not below 512 keys (256
 // a shard, 5 heads 15.4 / 15.9: the merge costs more).  More stages (loads three
@@ -203,7 +198,7 @@ void attention_kernel(AttnParams p) {
         const int r = 32 * t + col;
 #pragma unroll
         for (int ds = 0; ds < 8; ++ds) {
-          const bf16x8 kf = lds_read_b128(ks + r * RP + (((2 * ds + h) ^ (r & 15)) << 4));
+          const bf16x8 kf = lds_read<bf16x8>(ks + r * RP + (((2 * ds + h) ^ (r & 15)) << 4));
           sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ds], sacc[t], 0, 0, 0);
         }
       }

@@ -26,9 +26,6 @@
 #include "device_math.h"
 #include "lds_dma.h"
 
-// s_waitcnt with only the LDS / scalar-memory counter constrained (gfx9 encoding)
-#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt((((n) & 15) << 8) | 0xF | (0x3 << 14) | (0x7 << 4))
-
 namespace partir {
 namespace {
 
@@ -62,21 +59,6 @@ constexpr int PHI_BYTES = PHI_N * 8;
 
 template <typename T>
 __device__ __forceinline__ T pick3(int g, T a, T b, T c) { return g == 0 ? a : (g == 1 ? b : c); }
-
-// LDS tile layout: [row][64 k] = 128-byte rows of eight 16-byte chunks; chunk
-// c of row r sits at position c ^ swz(r), swz(r) = bit1(r) | bit3(r) << 1 |
-// bit2(r) << 2.  A fragment read takes 16 rows (lane % 16) at 4 chunks
-// (lane / 16); the LDS serves it 8 lanes of each half-wave at a time, i.e.
-// 8 rows at two chunks 2 apart, and swz gives the 4 rows of each parity
-// distinct bits 0 and 2, so the 16 reads hit 16 different bank groups (as do
-// any 16 consecutive lanes: the 8 rows of each parity get all 8 values).
-__device__ __forceinline__ int swz(int r) { return ((r >> 1) & 1) | (((r >> 3) & 1) << 1) | (((r >> 2) & 1) << 2); }
-// MN-major tile layout: [k][256 columns] = 512-byte rows of 32 chunks; chunk
-// c of k row r sits at position c ^ mn_swz(r).  A transposed fragment read
-// covers 4 k rows x 16 columns per 16-lane group, groups 0 and 1 (one pass)
-// on rows 8 apart: the 4 (r & 3) term spreads the 4 rows over the banks, the
-// 2 bit3(r) term keeps the two groups apart.
-__device__ __forceinline__ int mn_swz(int r) { return (4 * (r & 3)) ^ (2 * ((r >> 3) & 1)); }
 
 // PARTS: operands in device-local arrays (`t`, a kernel argument); else the
 // plain pointers of `p` and t is unused.
@@ -167,7 +149,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   // Per k tile each wave issues 4 + 4 wave-wide 16-byte loads; load j of wave
   // w fills rows 64 j + 8 w .. +8 of the operand tile (1 KiB of LDS written
   // lane by lane).  Lane L takes row +L/8, LDS chunk L%8, i.e. global chunk
-  // (L%8) ^ swz(row).  One descriptor per 64-row block bounds the valid rows.
+  // (L%8) ^ gemm_swz(row).  One descriptor per 64-row block bounds the valid rows.
   const uint16_t* Bg = pick3(grp, p.B[0], p.B[1], p.B[2]);
   const uint16_t* At = p.A + (int64_t)row0 * p.lda;
   const uint16_t* Btile = Bg + (int64_t)col0 * p.ldb;
@@ -205,7 +187,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   int b_kpart = 0;
   int b_kend = (PARTS && t->b_nrows) ? t->b_kcols : 0;
   const int lrow = RB * wave + lane / CPR;
-  const int lchunk = (lane % CPR) ^ swz(lrow);
+  const int lchunk = (lane % CPR) ^ gemm_swz(lrow);
   const uint32_t a_voff = (uint32_t)(lrow * p.lda * 2 + lchunk * 16);
   const uint32_t b_voff = (uint32_t)(lrow * p.ldb * 2 + lchunk * 16);
   const int lds_w = wave * 1024;
@@ -217,7 +199,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   // transposed fragment reads below conflict-free.  A descriptor per k tile
   // bounds the rows at the end of K (rows past it read as zero).
   const int mn_r = 2 * wave + (lane >> 5);
-  const int mn_chunk = (lane & 31) ^ mn_swz(mn_r);
+  const int mn_chunk = (lane & 31) ^ gemm_mn_swz<256>(mn_r);
   const uint32_t a_mvoff = AMN ? (uint32_t)(mn_r * p.lda * 2 + mn_chunk * 16) : 0u;
   const uint32_t b_mvoff = BMN ? (uint32_t)(mn_r * p.ldb * 2 + mn_chunk * 16) : 0u;
   // What the last k row of an MN-major operand lacks of a whole leading dim.
@@ -288,7 +270,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   // fragment is 16 rows (of A or B^T) x 32 k, lane l holding row l % 16 at
   // k = 8 (l / 16) .. +7, and the 16 x 16 result leaves lane l with output row
   // l % 16 at the 4 consecutive output columns 4 (l / 16) .. +3.
-  const int fsw = swz(lane & 15);
+  const int fsw = gemm_swz(lane & 15);
   const int g16 = lane >> 4;
   const int a_rd = (wm * 128 + (lane & 15)) * BK * 2;
   const int b_rd = OPB + (wn * 64 + (lane & 15)) * BK * 2;
@@ -309,7 +291,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
   // K-contiguous fragment.
   const int j16 = lane & 15;
   const int mn_row = 8 * g16 + (j16 >> 2);
-  const int mn_sw = mn_swz(mn_row);
+  const int mn_sw = gemm_mn_swz<256>(mn_row);
   const int mn_col = 4 * (j16 & 3);
   auto mn_frag = [&](const char* op, int ks, int bc) -> bf16x8 {
     const int col = bc + mn_col;
@@ -421,7 +403,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
     // K-contiguous streams: wave w4 owns rows r0 + 32 w4 .. +31 of its
     // operand (r0 = 128 x its half); load q fills rows 8 q .. 8 q + 7 of
     // those, lane L taking row L/8 and LDS chunk L%8 = global chunk
-    // (L%8) ^ swz(row), swz(row) = swz(8 (q & 1) + L/8).  One descriptor
+    // (L%8) ^ gemm_swz(row), gemm_swz(row) = gemm_swz(8 (q & 1) + L/8).  One descriptor
     // bounds the 32 rows; the K offset is the scalar offset.
     const int lr = lane >> 3;
     const int a_r0 = ah * 128 + 32 * w4, b_r0 = bh * 128 + 32 * w4;
@@ -450,8 +432,8 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
     uint32_t a_lo[2], b_lo[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      a_lo[e] = (uint32_t)(lr * p.lda * 2 + (((lane & 7) ^ swz(8 * e + lr)) << 4));
-      b_lo[e] = (uint32_t)(lr * p.ldb * 2 + (((lane & 7) ^ swz(8 * e + lr)) << 4));
+      a_lo[e] = (uint32_t)(lr * p.lda * 2 + (((lane & 7) ^ gemm_swz(8 * e + lr)) << 4));
+      b_lo[e] = (uint32_t)(lr * p.ldb * 2 + (((lane & 7) ^ gemm_swz(8 * e + lr)) << 4));
     }
     // MN-major B: wave w4 owns k rows 32 bh + 8 w4 .. +7; load q fills k rows
     // 2 q and 2 q + 1 of those, lane L taking row L/32 and LDS chunk L%32 =
@@ -461,7 +443,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int kr = 32 * bh + 8 * w4 + 2 * q + (lane >> 5);
-      b_mv[q] = BMN ? (uint32_t)(kr * p.ldb * 2 + (((lane & 31) ^ mn_swz(kr)) << 4)) : 0u;
+      b_mv[q] = BMN ? (uint32_t)(kr * p.ldb * 2 + (((lane & 31) ^ gemm_mn_swz<256>(kr)) << 4)) : 0u;
     }
     int b_kpart = 0;
     int b_kend = (PARTS && t->b_nrows) ? t->b_kcols : 0;
@@ -473,7 +455,7 @@ __device__ __forceinline__ void gemm_body(const GemmParams& p, const GemmParts* 
     };
     // K-contiguous chunk e-parity mask: chunks past the end of K read zero
     auto kmask = [&](int kb, int e) -> uint32_t {
-      return (kb + (((lane & 7) ^ swz(8 * e + lr)) << 3) < k_end) ? 0u : OOB;
+      return (kb + (((lane & 7) ^ gemm_swz(8 * e + lr)) << 3) < k_end) ? 0u : OOB;
     };
     auto prep_a = [&](int kt, int buf) -> LoadSet {
       LoadSet L;

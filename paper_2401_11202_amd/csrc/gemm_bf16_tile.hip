@@ -34,9 +34,6 @@
 #include "device_math.h"
 #include "lds_dma.h"
 
-// s_waitcnt with only the LDS / scalar-memory counter constrained (gfx9 encoding)
-#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt((((n) & 15) << 8) | 0xF | (0x3 << 14) | (0x7 << 4))
-
 namespace partir {
 namespace {
 
@@ -51,25 +48,6 @@ constexpr uint32_t OOB = 0x80000000u;          // offset that reads as zero
 
 template <typename T>
 __device__ __forceinline__ T pick3(int g, T a, T b, T c) { return g == 0 ? a : (g == 1 ? b : c); }
-
-// K-contiguous tile: 128-byte rows of eight 16-byte chunks, chunk c of row r
-// at position c ^ swz(r) (conflict-free 16-row fragment reads, as in
-// gemm_bf16.hip).
-__device__ __forceinline__ int swz(int r) { return ((r >> 1) & 1) | (((r >> 3) & 1) << 1) | (((r >> 2) & 1) << 2); }
-// MN-major tile of W columns: k rows of 2 W bytes, 16-byte chunk c of k row r
-// at position c ^ mn_swz(r).  A transposed read pass covers 32 bytes of the
-// rows r0 .. r0 + 3 and r0 + 8 .. r0 + 11, which must fall on different
-// banks: with 256-byte rows (W = 128) by the row's bits 0, 1 and 3; with
-// 128-byte rows (W = 64) bit 0 already selects the other half of the banks.
-template <int W>
-__device__ __forceinline__ int mn_swz(int r) {
-  return W == 128 ? ((4 * (r & 3)) ^ (2 * ((r >> 3) & 1))) : ((2 * (r & 2)) ^ (2 * ((r >> 3) & 1)));
-}
-
-// Fragment read through a restrict pointer: without the alias scope the wait
-// insertion makes every read wait for the LDS DMA in flight (which fills
-// other stages).
-__device__ __forceinline__ bf16x8 lds_read_b128(const char* __restrict__ p) { return *(const bf16x8*)p; }
 
 template <int BM, int BN, int WN, int NS, int AMN, int BMN, int PARTS>
 __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* t) {
@@ -119,7 +97,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
 
   // ---- global -> LDS loads ----------------------------------------------------
   // K-contiguous operand: load j of wave w fills tile rows 8 (NW j + w) .. +7;
-  // lane L takes row +L/8 and LDS chunk L%8 = global chunk (L%8) ^ swz(row).
+  // lane L takes row +L/8 and LDS chunk L%8 = global chunk (L%8) ^ gemm_swz(row).
   // One descriptor per 64 rows bounds the valid rows (rows past it read zero).
   // MN-major operand: load j of wave w fills R = 512 / W k rows at R (NW j + w);
   // a descriptor per K tile bounds the k rows at the end of K and the last one
@@ -167,7 +145,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
     }
   };
   const int lrow = 8 * wave + (lane >> 3);
-  const int lchunk = (lane & 7) ^ swz(lrow);
+  const int lchunk = (lane & 7) ^ gemm_swz(lrow);
   constexpr int RL = 8 * NW, LPB = 64 / RL;   // rows per load of all waves, loads per 64 rows
   uint32_t a_voff[LPB], b_voff[LPB];
 #pragma unroll
@@ -181,14 +159,14 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
     const int r0 = R * wave + lane / (BM / 8);
 #pragma unroll
     for (int j = 0; j < LA; ++j)
-      a_mv[j] = (uint32_t)((NW * R * j + r0) * p.lda * 2 + (((lane % (BM / 8)) ^ mn_swz<BM>(r0)) << 4));
+      a_mv[j] = (uint32_t)((NW * R * j + r0) * p.lda * 2 + (((lane % (BM / 8)) ^ gemm_mn_swz<BM>(r0)) << 4));
   }
   if (BMN) {
     constexpr int R = 512 / BN;
     const int r0 = R * wave + lane / (BN / 8);
 #pragma unroll
     for (int j = 0; j < LB; ++j)
-      b_mv[j] = (uint32_t)((NW * R * j + r0) * p.ldb * 2 + (((lane % (BN / 8)) ^ mn_swz<BN>(r0)) << 4));
+      b_mv[j] = (uint32_t)((NW * R * j + r0) * p.ldb * 2 + (((lane % (BN / 8)) ^ gemm_mn_swz<BN>(r0)) << 4));
   }
   // what the last k row of an MN-major operand lacks of a whole leading dim
   const uint32_t a_cut = (uint32_t)(p.lda - (p.M - row0)) * 2, b_cut = (uint32_t)(p.ldb - (p.N - col0)) * 2;
@@ -228,13 +206,13 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
 
   // ---- MFMA operand reads (fragment layouts as in gemm_bf16.hip) --------------
   const int g16 = lane >> 4, j16 = lane & 15;
-  const int fsw = swz(j16);
+  const int fsw = gemm_swz(j16);
   const int mn_row = 8 * g16 + (j16 >> 2);
   const int mn_col = 4 * (j16 & 3);
   auto mn_frag = [&](const char* op, auto width, int ks, int bc) -> bf16x8 {
     constexpr int W = decltype(width)::value;
     const int col = bc + mn_col;
-    const char* pl = op + (32 * ks + mn_row) * (2 * W) + (((col >> 3) ^ mn_swz<W>(mn_row)) << 4) + ((col & 4) << 1);
+    const char* pl = op + (32 * ks + mn_row) * (2 * W) + (((col >> 3) ^ gemm_mn_swz<W>(mn_row)) << 4) + ((col & 4) << 1);
     const i16x4 lo = lds_read_tr16(pl);
     const i16x4 hi = lds_read_tr16(pl + 4 * 2 * W);
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -246,12 +224,12 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const GemmParts* 
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       if constexpr (AMN) a[i] = mn_frag(pa, std::integral_constant<int, BM>{}, ks, wm * WTM + i * 16);
-      else a[i] = lds_read_b128(pa + (wm * WTM + i * 16 + j16) * (BK * 2) + ko);
+      else a[i] = lds_read<bf16x8>(pa + (wm * WTM + i * 16 + j16) * (BK * 2) + ko);
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       if constexpr (BMN) b[j] = mn_frag(pb, std::integral_constant<int, BN>{}, ks, wn * WTN + j * 16);
-      else b[j] = lds_read_b128(pb + (wn * WTN + j * 16 + j16) * (BK * 2) + ko);
+      else b[j] = lds_read<bf16x8>(pb + (wn * WTN + j * 16 + j16) * (BK * 2) + ko);
     }
   };
   f32x4 acc[MI][NJ];

@@ -22,9 +22,6 @@
 #include "kernels.h"
 #include "lds_dma.h"
 
-// s_waitcnt with only the LDS / scalar-memory counter constrained (gfx9 encoding)
-#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt((((n) & 15) << 8) | 0xF | (0x3 << 14) | (0x7 << 4))
-
 namespace partir {
 namespace {
 
@@ -45,11 +42,6 @@ __device__ __forceinline__ int swz(int r) { return (r & 6) | ((r >> 3) & 1); }
 // rows 8 s + e and 8 s + 4 + e that one read takes 128 bytes of fall on
 // different halves of the banks.
 __device__ __forceinline__ int kn_swz(int r) { return 8 * ((r >> 2) & 1); }
-
-// Reads through restrict pointers: without the alias scope the wait insertion
-// makes every read wait for the LDS DMA in flight (which fills other stages).
-__device__ __forceinline__ f32x4 lds_read4(const char* __restrict__ p) { return *(const f32x4*)p; }
-__device__ __forceinline__ float lds_read1(const char* __restrict__ p) { return *(const float*)p; }
 
 template <int BT, int BKN>
 __device__ __forceinline__ void gemm_f32_body(const GemmF32Params& p) {
@@ -144,16 +136,16 @@ __device__ __forceinline__ void gemm_f32_body(const GemmF32Params& p) {
     const char* pb = pa + OP;
     const int ko = ((2 * s + h) ^ swz(l32)) << 4;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) a[i] = lds_read4(pa + (wm * WT + 32 * i + l32) * (BK * 4) + ko);
+    for (int i = 0; i < NB; ++i) a[i] = lds_read<f32x4>(pa + (wm * WT + 32 * i + l32) * (BK * 4) + ko);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       if constexpr (BKN) {
         const int k = 8 * s + 4 * h, n = wn * WT + 32 * j + l32;
         const char* q = pb + k * (BT * 4) + ((((n >> 2) ^ kn_swz(k)) << 4) | ((n & 3) << 2));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) b[j][e] = lds_read1(q + e * (BT * 4));   // k .. k + 3 share kn_swz
+        for (int e = 0; e < 4; ++e) b[j][e] = lds_read<float>(q + e * (BT * 4));   // k .. k + 3 share kn_swz
       } else {
-        b[j] = lds_read4(pb + (wn * WT + 32 * j + l32) * (BK * 4) + ko);
+        b[j] = lds_read<f32x4>(pb + (wn * WT + 32 * j + l32) * (BK * 4) + ko);
       }
     }
   };

@@ -642,8 +642,8 @@ int validate_matmul(const MatmulArgs& a, bool with_ptrs) {
   // within 2^31.
   if (a.ab == PARTIR_BF16 && ((a_used && a.lda > kBf16MaxLd) || (b_used && a.ldb > kBf16MaxLd)))
     return fail(PARTIR_E_SHAPE, "bf16 operands: leading dims above 2^24 elements are not addressable");
-  // output tiles (64 x 64 at the smallest, never straddling a shard) times
-  // K shards index the grid in 32 bits
+  // output tiles times K shards index the grid in 32 bits; 64 x 64 tiles
+  // counted per shard are the upper bound of what any plan launches
   const int64_t rm = a.tile_axis == PARTIR_AXIS_M ? a.R : 1;
   if (c_used && rm * cdiv(a.M / rm, 64) * rn * cdiv(a.N / rn, 64) * (int64_t)rk > ((int64_t)1 << 31) - 1)
     return fail(PARTIR_E_SHAPE, "C[%lld,%lld] with R=%d has more output tiles than a launch can index",
