@@ -114,3 +114,30 @@ def test_a_fused_sum_is_one_accumulator(rows, R, layout):
     part = P.loop_matmul(Ad[:rows], few, sum="K", R=R, sum_impl="fused", b_layout=layout, out_dtype=torch.float32)
     torch.cuda.synchronize()
     assert torch.equal(part, whole[:rows, :512])
+
+
+# the weight gradients: both operands stored [K, .], K = T ending inside a K
+# tile, ragged in both directions; words of both products' plans
+@pytest.mark.parametrize("T,D,F,words", [
+    (136, 136, 200, "grid 12 WGs; read in place: A as [K, M] B as [K, N]; workgroup tiles of 64 x 64"),
+    (136, 2312, 392, "grid 259 WGs; read in place: A as [K, M] B as [K, N]; workgroup tiles of 64 x 64"),
+    (2056, 136, 392, "21 tiles as 4 K parts of 9 K tiles each; workgroup tiles of 64 x 64"),
+    (136, 1032, 2312, "grid 171 WGs; read in place: A as [K, M] B as [K, N]; workgroup tiles of 128 x 128"),
+    (136, 1544, 3080, "grid 325 WGs; read in place: A as [K, M] B as [K, N]; workgroup tiles of 128 x 128"),
+    (4104, 136, 3080, "50 tiles as 4 K parts of 17 K tiles each; workgroup tiles of 128 x 128"),
+])
+def test_operands_stored_k_m(T, D, F, words):
+    """Entries in {-1, 0, 1} and the identity activation: Z and dH are integers
+    that bf16 holds, so the gradients are exact."""
+    X, W1 = I.small_ints(206, 0, (T, D), -1, 1), I.small_ints(206, 1, (D, F), -1, 1)
+    W2, dY = I.small_ints(206, 2, (F, D), -1, 1), I.small_ints(206, 3, (T, D), -1, 1)
+    Z, dH = X.f64() @ W1.f64(), dY.f64() @ W2.f64().T
+    assert max(np.abs(Z).max(), np.abs(dH).max()) <= 256
+    say(f"A [K, M], B [K, N]: T={T} D={D} F={F}")
+    _, dW1, dW2 = P.mlp_block_backward(*(t.to_device() for t in (X, W1, W2, dY)), act="none")
+    torch.cuda.synchronize()
+    text = P.lib().partir_last_plan_text().decode()
+    for name in ("bwd.dw1", "bwd.dw2"):
+        line = next(l for l in text.splitlines() if name in l)
+        assert words in line, line
+    assert np.array_equal(host(dW1), X.f64().T @ dH) and np.array_equal(host(dW2), Z.T @ dY.f64())

@@ -43,6 +43,48 @@ CALLS = [
 ]
 
 
+# every entry point that executes (the device pointers of one call alike)
+ENTRY = {
+    "loop_matmul": CALLS[0][0],
+    "mlp_block": CALLS[1][0],
+    "attn_block": CALLS[2][0],
+    "decoder_layer": CALLS[3][0],
+    "mlp_block_sharded": CALLS[4][0],
+    "mlp_block_train": lambda L: L.partir_mlp_block_train(D, D, D, D, D, D, D, 1000, 8200, 4104, P.BF16, P.F32,
+                                                          P.ACT_GELU, 1, 1, D, 1 << 34, None),
+    "mlp_block_backward": lambda L: L.partir_mlp_block_backward(D, D, D, D, D, D, D, D, D, D, D, 1536, 2560, 10240,
+                                                                P.ACT_GELU, 2, 4, D, 1 << 34, None),
+    "mlp_block_backward, Z recomputed, no bias gradients": lambda L: L.partir_mlp_block_backward(
+        D, D, None, D, D, None, D, D, None, D, None, 520, 200, 336, P.ACT_GELU, 5, 2, D, 1 << 34, None),
+    "attn_block_train": lambda L: L.partir_attn_block_train(D, D, D, D, D, D, D, 2, 256, 1024, 8, 128, 1, 0.0, P.BF16,
+                                                            P.F32, 1, 8, D, 1 << 34, None),
+    "attn_block_backward": lambda L: L.partir_attn_block_backward(D, D, D, D, D, D, D, D, D, D, D, D, 4, 2048, 4096, 32,
+                                                                  128, 1, 0.0, 2, 8, D, 1 << 34, None),
+    "attention": lambda L: L.partir_attention(D, D, D, D, 1, 8192, 2, 128, 1, 0.0, 4, D, 1 << 34, None),
+    "attention_train": lambda L: L.partir_attention_train(D, D, D, D, D, 1, 512, 2, 128, 0, 0.0, 1, D, 1 << 34, None),
+    "attention_backward": lambda L: L.partir_attention_backward(D, D, D, D, D, D, D, D, D, 1, 512, 2, 128, 1, 0.0, D,
+                                                                1 << 34, None),
+    "decoder_layer_sharded": lambda L: L.partir_decoder_layer_sharded(
+        parts(8), D, D, 1e-6, parts(8), parts(8), parts(8), parts(8), parts(8), parts(8), 2, 1024, 2048, 16, 128, 5632,
+        2, 4, D, 1 << 34, None),
+}
+
+
+@pytest.mark.parametrize("name", ENTRY)
+def test_deferred_text_is_the_text_of_the_plan_that_runs(name, monkeypatch, capfd):
+    """PARTIR_DUMP_PLAN formats the plan that is executed, pointers and all;
+    without it the text is planned again from the sizes alone."""
+    call = ENTRY[name]
+    monkeypatch.setenv("PARTIR_DUMP_PLAN", "1")
+    assert P.STATUS[call(P.lib())] == "PARTIR_E_HIP", P.lib().partir_last_error().decode()
+    want = last()
+    assert want.startswith(name.split(",")[0] + ":") and want in capfd.readouterr().err
+    monkeypatch.delenv("PARTIR_DUMP_PLAN")
+    P.plan_loop_matmul(8, 8, 8)
+    assert P.STATUS[call(P.lib())] == "PARTIR_E_HIP"
+    assert last() == want and capfd.readouterr().err == ""
+
+
 @pytest.mark.parametrize("call,plan", CALLS)
 def test_text_of_a_call_is_the_plan_querys(call, plan):
     want = plan()["text"]
