@@ -692,7 +692,8 @@ GemmSpec matmul_spec(const MatmulArgs& a) {
 }
 
 // A split #sum asks for the partials of every shard, also where the planner
-// then needs fewer.
+// then needs fewer or none: which calls partir_loop_matmul_noalloc refuses does
+// not hang on the planner's choice of tile.
 size_t matmul_ws_bytes(const GemmSpec& g) {
   const size_t need = gemm_ws_bytes(g);
   return gemm_uses_splitk(g) ? std::max(need, align_up((size_t)g.rk * g.M * g.N * sizeof(float))) : need;
