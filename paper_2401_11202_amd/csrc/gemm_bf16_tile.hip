@@ -24,8 +24,10 @@
 // four waves a CU on two stages each (4096^3 119 us; with eight waves 122,
 // their smaller wave tiles read more LDS).  Per K tile (2048 x 2048 x 8192,
 // one workgroup a CU) the MFMAs alone take 0.29 us, with the fragment reads
-// 0.40, with the loads 0.52: LDS and L1 traffic per MFMA bound it, which is why
-// the 256-wide tile is better on whole waves (4096^3: 95 us).  Before / after
+// 0.40, with the loads 0.52: the waits for loads and fragments bound it, not a
+// unit at its rate (200 x 16384 x 4096, counters: matrix cores busy 0.32 of
+// cycles, LDS reads 0.25, HBM 3.5 TB/s), and the 256-wide tile with fewer of
+// them per MFMA is better on whole waves (4096^3: 95 us).  Before / after
 // this kernel (launch time, us): 2048^3 44 -> 22, 200 x 16384 x 4096 57 -> 36,
 // 200 x 4096 x 16384 108 -> 42 (4 K parts), 512 x 1024 x 256 13 -> 7 (64-wide).
 #include <type_traits>
